@@ -135,6 +135,10 @@ constexpr int kPreMax = 1024;
 
 hipError_t launch_conv_bf16(const ConvArgs &a, Loader ld, hipStream_t s);
 hipError_t launch_conv_f32(const ConvArgs &a, Loader ld, hipStream_t s);
+// 256 x 256 tiles (conv_pp.hip); hipErrorNotSupported, having launched
+// nothing, when conv_pp_supported says no.
+bool conv_pp_supported(const ConvArgs &a, Loader ld);
+hipError_t launch_conv_pp(const ConvArgs &a, Loader ld, hipStream_t s);
 // The ordered sum of an fp32 convolution's slices (a.splits > 1), then its
 // bias, residual and activation, into a.y.
 hipError_t launch_f32_split_reduce(const ConvArgs &a, hipStream_t s);
