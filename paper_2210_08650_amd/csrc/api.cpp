@@ -617,7 +617,7 @@ hipError_t run_conv(const Ctx &c, const ConvSpec &cs, const void *x, const Act &
   a.splits = cs.splits;
   a.part = c.part;
   hipError_t r = timed(c.s, F_CONV_F32, flops, bytes, [&] { return launch_conv_f32(a, ld, c.s); });
-  if (r != hipSuccess || cs.splits <= 1) return r;
+  if (r != hipSuccess || f32_seq(a, ld)) return r;
   const double pbytes = 4.0 * a.M * a.N * (cs.splits + 1);
   return timed(c.s, F_SPLIT_SUM, (double)a.M * a.N * cs.splits, pbytes,
                [&] { return launch_f32_split_reduce(a, c.s); });

@@ -9,7 +9,7 @@
 // bf16 path: v_mfma_f32_32x32x16_bf16 with fp32 accumulation, k-tile 64,
 // 256 threads = 4 waves in a 2 x 2 grid, double-buffered LDS with one barrier
 // per k-tile, global loads of the next tile in flight during the MFMAs.
-// fp32 path: v_mfma_f32_32x32x2f32, k-tile 16, same structure.
+// (fp32: conv_f32.hip.)
 //
 // Every output element's reduction visits the k-tiles in order and, inside a
 // tile, the MFMA k-steps in order, independent of the tile shape (BM, BN) and
@@ -31,33 +31,6 @@ constexpr int kThreads = 256;
 
 constexpr int BK = 64;         // k-tile (bf16 elements)
 constexpr int LDSW = BK + 8;   // LDS row pitch in elements: 144 B spreads rows over banks
-
-// Per-row state of the rows a thread gathers for the A tile.
-struct RowState {
-  int base;  // element offset of the row's image (NHWC / NCHW) or of the row (GEMM)
-  int hi0;   // ho * stride - pad  (large negative: row beyond M)
-  int wi0;   // wo * stride - pad
-};
-
-template <int LD>
-__device__ __forceinline__ RowState make_row(const ConvArgs &a, int m) {
-  RowState r;
-  if (m >= a.M) {
-    r.base = 0; r.hi0 = -(1 << 28); r.wi0 = 0;
-    return r;
-  }
-  if (LD == LD_GEMM) {
-    r.base = m * (a.lda ? a.lda : a.K); r.hi0 = 0; r.wi0 = 0;
-    return r;
-  }
-  const int hw = a.Ho * a.Wo;
-  const int n = m / hw, rem = m - n * hw;
-  const int ho = rem / a.Wo, wo = rem - ho * a.Wo;
-  r.base = n * a.H * a.W * a.C;
-  r.hi0 = ho * a.stride - a.pad;
-  r.wi0 = wo * a.stride - a.pad;
-  return r;
-}
 
 // Gather the 8 consecutive k values [k0, k0 + 8) of one im2col row.
 template <int LD>
@@ -1899,218 +1872,6 @@ hipError_t launch_bf16_ld(const ConvArgs &a, hipStream_t s) {
   return launch_bf16_cfg<128, 128, LD>(a, s);
 }
 
-// ------------------------------------------------------------------ fp32
-
-constexpr int BKF = 16;        // k-tile (fp32 elements)
-constexpr int LDSF = BKF + 4;  // LDS row pitch in floats (80 B)
-
-template <int LD>
-__device__ __forceinline__ float4 load_a_chunk_f32(const ConvArgs &a, const RowState &r, int k0,
-                                                   int kh_, int kw_, int c0) {
-  const float *x = static_cast<const float *>(a.x);
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (LD == LD_GEMM) {
-    if (r.hi0 >= 0) v = *reinterpret_cast<const float4 *>(x + r.base + k0);
-  } else if (LD == LD_NHWC) {
-    const int hi = r.hi0 + kh_, wi = r.wi0 + kw_;
-    if ((unsigned)hi < (unsigned)a.H && (unsigned)wi < (unsigned)a.W)
-      v = *reinterpret_cast<const float4 *>(x + r.base + (hi * a.W + wi) * a.C + c0);
-  } else {  // LD_NCHW element gather, k = (c, u, v)
-    if (r.hi0 > -(1 << 27)) {
-      float e[4];
-      const int khw = a.kh * a.kw;
-      int c = k0 / khw, rem = k0 - c * khw;
-      int u = rem / a.kw, vv = rem - u * a.kw;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int hi = r.hi0 + u, wi = r.wi0 + vv;
-        e[j] = (k0 + j < a.K && (unsigned)hi < (unsigned)a.H && (unsigned)wi < (unsigned)a.W)
-                   ? x[r.base + (c * a.H + hi) * a.W + wi]
-                   : 0.0f;
-        if (++vv == a.kw) { vv = 0; if (++u == a.kh) { u = 0; ++c; } }
-      }
-      v = make_float4(e[0], e[1], e[2], e[3]);
-    }
-  }
-  return v;
-}
-
-template <int BM, int BN, int LD>
-__global__ __launch_bounds__(kThreads) void conv_f32_kernel(ConvArgs a) {
-  constexpr int WN = 2;
-  constexpr int TM = BM / 64, TN = BN / 64;
-  constexpr int A_PER = BM * (BKF / 4) / kThreads;  // float4 chunks per thread
-  constexpr int B_PER = BN * (BKF / 4) / kThreads;
-  static_assert(TM >= 1 && TN >= 1 && A_PER >= 1 && B_PER >= 1, "tile");
-
-  __shared__ __attribute__((aligned(16))) float smem[2 * (BM + BN) * LDSF];
-
-  const int tiles_n = (a.N + BN - 1) / BN;
-  const int tile = a.rev ? (int)gridDim.x - 1 - xcd_remap(blockIdx.x, gridDim.x) : xcd_remap(blockIdx.x, gridDim.x);
-  const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
-
-  const int t = threadIdx.x;
-  const int kc = t & 3;   // float4 chunk of the 16-wide k-tile
-  const int r0 = t >> 2;  // first row; then every 64th
-
-  RowState rs[A_PER];
-#pragma unroll
-  for (int i = 0; i < A_PER; ++i) rs[i] = make_row<LD>(a, m0 + r0 + 64 * i);
-
-  const float *wp = static_cast<const float *>(a.w);
-  float4 ra[A_PER], rb[B_PER];
-  auto load_tile = [&](int kt) {
-    const int kbase = kt * BKF;
-    int kh_ = 0, kw_ = 0, c0 = 0;
-    if (LD == LD_NHWC) {  // C % 16 == 0: the k-tile lies in one tap
-      const int tap = kbase / a.C;
-      c0 = kbase - tap * a.C + kc * 4;
-      kh_ = tap / a.kw;
-      kw_ = tap - kh_ * a.kw;
-    }
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i) ra[i] = load_a_chunk_f32<LD>(a, rs[i], kbase + kc * 4, kh_, kw_, c0);
-#pragma unroll
-    for (int j = 0; j < B_PER; ++j) {
-      const int n = n0 + r0 + 64 * j;
-      rb[j] = (n < a.N) ? *reinterpret_cast<const float4 *>(wp + (size_t)n * a.Kp + kbase + kc * 4)
-                        : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  auto store_tile = [&](int buf) {
-    float *As = smem + buf * (BM + BN) * LDSF;
-    float *Bs = As + BM * LDSF;
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i) *reinterpret_cast<float4 *>(As + (r0 + 64 * i) * LDSF + kc * 4) = ra[i];
-#pragma unroll
-    for (int j = 0; j < B_PER; ++j) *reinterpret_cast<float4 *>(Bs + (r0 + 64 * j) * LDSF + kc * 4) = rb[j];
-  };
-
-  const int lane = t & 63, wave = t >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int lrow = lane & 31, lk = (lane >> 5) * 8;
-
-  f32x16_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-  // k-tiles [kt0, kt1): slice blockIdx.y of a split reduction, or all of them.
-  const int nk_all = a.Kp / BKF;
-  const int S = a.splits > 1 ? a.splits : 1;
-  const int kt0 = (int)((int64_t)nk_all * blockIdx.y / S), kt1 = (int)((int64_t)nk_all * (blockIdx.y + 1) / S);
-  load_tile(kt0);
-  store_tile(0);
-  __syncthreads();
-  for (int kt = kt0; kt < kt1; ++kt) {
-    const int cur = (kt - kt0) & 1;
-    if (kt + 1 < kt1) load_tile(kt + 1);
-    const float *As = smem + cur * (BM + BN) * LDSF + (wm * TM * 32 + lrow) * LDSF + lk;
-    const float *Bs = smem + cur * (BM + BN) * LDSF + BM * LDSF + (wn * TN * 32 + lrow) * LDSF + lk;
-    // Lane half h feeds k = 8h + s at step s to both operands, so the 8 steps
-    // cover the 16 k of the tile exactly once.
-    float av[TM][8], bv[TN][8];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const float4 p = *reinterpret_cast<const float4 *>(As + i * 32 * LDSF);
-      const float4 q = *reinterpret_cast<const float4 *>(As + i * 32 * LDSF + 4);
-      av[i][0] = p.x; av[i][1] = p.y; av[i][2] = p.z; av[i][3] = p.w;
-      av[i][4] = q.x; av[i][5] = q.y; av[i][6] = q.z; av[i][7] = q.w;
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const float4 p = *reinterpret_cast<const float4 *>(Bs + j * 32 * LDSF);
-      const float4 q = *reinterpret_cast<const float4 *>(Bs + j * 32 * LDSF + 4);
-      bv[j][0] = p.x; bv[j][1] = p.y; bv[j][2] = p.z; bv[j][3] = p.w;
-      bv[j][4] = q.x; bv[j][5] = q.y; bv[j][6] = q.z; bv[j][7] = q.w;
-    }
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i][s], bv[j][s], acc[i][j], 0, 0, 0);
-    if (kt + 1 < kt1) store_tile(cur ^ 1);
-    __syncthreads();
-  }
-
-  if (S > 1) {  // partial sums of this slice; bias and activation come after the sum
-    float *part = a.part + (int64_t)blockIdx.y * a.M * a.N;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int n = n0 + wn * TN * 32 + j * 32 + lrow;
-      if (n >= a.N) continue;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = m0 + wm * TM * 32 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (m < a.M) part[(int64_t)m * a.N + n] = acc[i][j][r];
-        }
-    }
-    return;
-  }
-  float *y = static_cast<float *>(a.y);
-  const float *res = static_cast<const float *>(a.res);
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = n0 + wn * TN * 32 + j * 32 + lrow;
-    if (n >= a.N) continue;
-    const float bvv = a.bias ? a.bias[n] : 0.0f;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * TM * 32 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (m >= a.M) continue;
-        float v = acc[i][j][r] + bvv;
-        if (res) v += res[(int64_t)m * a.ldr + n];
-        y[(int64_t)m * a.ldc + n] = epilogue_act(v, a.relu, a.gelu);
-      }
-    }
-  }
-}
-
-// Sum of the slices in slice order, then bias, residual and activation (the
-// unsplit epilogue's order), 4 channels per thread.
-__global__ void f32_split_reduce_kernel(ConvArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int ng = a.N / 4;
-  if (i >= (int64_t)a.M * ng) return;
-  const int64_t m = i / ng;
-  const int n = (int)(i - m * ng) * 4;
-  const int64_t stride = (int64_t)a.M * a.N;
-  float4 v = *reinterpret_cast<const float4 *>(a.part + m * a.N + n);
-  for (int sl = 1; sl < a.splits; ++sl) {
-    const float4 p = *reinterpret_cast<const float4 *>(a.part + sl * stride + m * a.N + n);
-    v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-  }
-  float o[4] = {v.x, v.y, v.z, v.w};
-  const float *res = static_cast<const float *>(a.res);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    float x = o[e] + (a.bias ? a.bias[n + e] : 0.0f);
-    if (res) x += res[m * a.ldr + n + e];
-    o[e] = epilogue_act(x, a.relu, a.gelu);
-  }
-  float *y = static_cast<float *>(a.y);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) y[m * a.ldc + n + e] = o[e];
-}
-
-template <int BM, int BN, int LD>
-hipError_t launch_f32_cfg(const ConvArgs &a, hipStream_t s) {
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  const int S = a.splits > 1 ? a.splits : 1;
-  if (S > 1 && (!a.part || a.N % 4 != 0 || a.Kp / BKF < S)) return hipErrorInvalidValue;
-  hapi_launch((conv_f32_kernel<BM, BN, LD>), dim3(tiles, S), dim3(kThreads), 0, s, a);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_conv_bf16(const ConvArgs &a, Loader ld, hipStream_t s) {
@@ -2168,23 +1929,6 @@ hipError_t launch_conv_bf16(const ConvArgs &a, Loader ld, hipStream_t s) {
       if (a.N % 8 != 0 || a.ldc % 8 != 0 || a.ldr % 8 != 0 || !ws_eligible(a, LD_NHWC8)) break;
       if (a.N <= 64) return launch_ws_cfg<128, 64, 2, 2, 3, LD_NHWC8, 1, 0, 2>(a, s);
       return launch_ws_cfg<128, 128, 2, 2, 2, LD_NHWC8, 1, 0, 2>(a, s);
-  }
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_f32_split_reduce(const ConvArgs &a, hipStream_t s) {
-  if (a.splits <= 1 || !a.part || a.N % 4 != 0) return hipErrorInvalidValue;
-  const int64_t items = (int64_t)a.M * (a.N / 4);
-  hapi_launch(f32_split_reduce_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_conv_f32(const ConvArgs &a, Loader ld, hipStream_t s) {
-  switch (ld) {
-    case LD_NHWC: return launch_f32_cfg<64, 64, LD_NHWC>(a, s);
-    case LD_GEMM: return launch_f32_cfg<64, 64, LD_GEMM>(a, s);
-    case LD_NCHW: return launch_f32_cfg<64, 64, LD_NCHW>(a, s);
-    default: break;
   }
   return hipErrorInvalidValue;
 }

@@ -50,5 +50,32 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 constexpr unsigned kOob = 0x80000000u;  // a byte offset outside every buffer range
 
+// Per-row state of the rows a thread gathers for the A tile.
+struct RowState {
+  int base;  // element offset of the row's image (NHWC / NCHW) or of the row (GEMM)
+  int hi0;   // ho * stride - pad  (large negative: row beyond M)
+  int wi0;   // wo * stride - pad
+};
+
+template <int LD>
+__device__ __forceinline__ RowState make_row(const ConvArgs &a, int m) {
+  RowState r;
+  if (m >= a.M) {
+    r.base = 0; r.hi0 = -(1 << 28); r.wi0 = 0;
+    return r;
+  }
+  if (LD == LD_GEMM) {
+    r.base = m * (a.lda ? a.lda : a.K); r.hi0 = 0; r.wi0 = 0;
+    return r;
+  }
+  const int hw = a.Ho * a.Wo;
+  const int n = m / hw, rem = m - n * hw;
+  const int ho = rem / a.Wo, wo = rem - ho * a.Wo;
+  r.base = n * a.H * a.W * a.C;
+  r.hi0 = ho * a.stride - a.pad;
+  r.wi0 = wo * a.stride - a.pad;
+  return r;
+}
+
 }  // namespace
 }  // namespace hapi

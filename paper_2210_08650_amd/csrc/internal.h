@@ -139,8 +139,11 @@ hipError_t launch_conv_f32(const ConvArgs &a, Loader ld, hipStream_t s);
 // nothing, when conv_pp_supported says no.
 bool conv_pp_supported(const ConvArgs &a, Loader ld);
 hipError_t launch_conv_pp(const ConvArgs &a, Loader ld, hipStream_t s);
-// The ordered sum of an fp32 convolution's slices (a.splits > 1), then its
-// bias, residual and activation, into a.y.
+// Whether launch_conv_f32 sums the slices itself (no partial sums, so no
+// launch_f32_split_reduce): a single slice, or enough tiles without them.
+bool f32_seq(const ConvArgs &a, Loader ld);
+// The ordered sum of an fp32 convolution's slices (!f32_seq), then its bias,
+// residual and activation, into a.y.
 hipError_t launch_f32_split_reduce(const ConvArgs &a, hipStream_t s);
 
 // Elementwise / memory-bound kernels; `bf16` selects the activation type.
