@@ -743,10 +743,15 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
   constexpr int NA = BM / (8 * CW), NB = BN / (8 * CW);  // DMA instructions per producer lane
   constexpr int NQ = NA + NB;
   constexpr int KS = BK / 16;
+  // k-tiles in flight or being read: with 1 x 1 fragments per wave and a deep
+  // ring, a stage is handed back one barrier later, so that no barrier waits
+  // for fragment reads to return.
+  constexpr bool LATE = TM * TN == 1 && STAGES >= 5;
+  constexpr int DEP = LATE ? STAGES - 1 : STAGES;
   using SM = PipeSmem<BM, BN, STAGES, EPI>;
   using Plan = WsPlan<NA, NB, LD, KW>;
   static_assert(NA * 8 * CW == BM && NB * 8 * CW == BN && TM >= 1 && TN >= 1, "tile");
-  static_assert(STAGES >= 2 && STAGES <= 4 && (STAGES - 2) * NQ < 64, "stages");
+  static_assert(STAGES >= 2 && (STAGES - 2) * NQ < 64, "stages");
   __shared__ __attribute__((aligned(16))) uint8_t smem_raw[SM::kBytes];
   uint16_t *smem = reinterpret_cast<uint16_t *>(smem_raw);
   __shared__ __attribute__((aligned(16))) float pre_s[PRE ? 2 * kPreMax : 4];
@@ -831,13 +836,13 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
       const int rpc = a.kh / 4, c = cb / rpc, u0 = (cb - c * rpc) * 4;
       return (unsigned)((((int64_t)c * a.H + u0) * a.W) * 2);
     };
-    int q = 0;  // next k-tile to issue
+    int q = 0, qs = 0;  // next k-tile to issue, and its stage
     // Before issuing k-tile q into stage q % STAGES: once STAGES - 1 tiles are
     // in flight, wait until k-tile q - STAGES + 1 has landed, then meet the
     // consumers at its barrier (which also frees the stage it reuses).
     auto gate = [&] {
-      if (q >= STAGES - 1) {
-        wait_vmcnt<(STAGES - 2) * NQ>();
+      if (q >= DEP - 1) {
+        wait_vmcnt<(DEP - 2) * NQ>();
         __builtin_amdgcn_s_barrier();
       }
     };
@@ -850,34 +855,37 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
       constexpr int tap = decltype(tc)::value;
       for (int cb = 0; cb < cpt; ++cb) {
         gate();
-        uint16_t *As = smem + (q % STAGES) * SM::kStage;
+        uint16_t *As = smem + qs * SM::kStage;
         const unsigned so = soff_a(cb);
 #pragma unroll
         for (int i = 0; i < NA; ++i)
           dma16(a.x, As + (pw * NA + i) * 512, pl.va[tap][i], so);
         issue_b(As + BM * BK);
         ++q;
+        qs = qs + 1 == STAGES ? 0 : qs + 1;
       }
     });
     if (LD == LD_CAT) {  // shortcut part: 1 x 1 on x2
       const int cpt2 = a.C2 / BK;
       for (int cb = 0; cb < cpt2; ++cb) {
         gate();
-        uint16_t *As = smem + (q % STAGES) * SM::kStage;
+        uint16_t *As = smem + qs * SM::kStage;
 #pragma unroll
         for (int i = 0; i < NA; ++i)
           dma16(a.x2, As + (pw * NA + i) * 512, pl.va2[LD == LD_CAT ? i : 0], (unsigned)(cb * BK * 2));
         issue_b(As + BM * BK);
         ++q;
+        qs = qs + 1 == STAGES ? 0 : qs + 1;
       }
     }
     // Drain: the last min(nk, STAGES - 1) barriers; k-tile b has nk - 1 - b
     // younger tiles in flight.
-    for (int b = max(0, nk - STAGES + 1); b < nk; ++b) {
+    for (int b = max(0, nk - DEP + 1); b < nk; ++b) {
       const int younger = nk - 1 - b;
-      if (STAGES >= 4 && younger >= 2) wait_vmcnt<(STAGES >= 4 ? 2 : 0) * NQ>();
-      else if (STAGES >= 3 && younger >= 1) wait_vmcnt<(STAGES >= 3 ? 1 : 0) * NQ>();
-      else wait_vmcnt<0>();
+      static_for<DEP - 1>([&](auto yc) {
+        constexpr int yv = decltype(yc)::value;
+        if (younger == yv) wait_vmcnt<yv * NQ>();
+      });
       __builtin_amdgcn_s_barrier();
     }
   } else {
@@ -895,6 +903,68 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) boff[j] = BM * BK + (wn * TN * 32 + j * 32 + lrow) * BK;
     const int sw = (lrow >> 1) & 7;
+    if constexpr (TM * TN == 1) {
+      // One MFMA per k-step cannot hide the latency of the next step's reads:
+      // the whole next k-tile's fragments are read while this one's MFMAs run
+      // (ResNet-50 b8 450 -> 428 us, b16 521 -> 481 us; with the later hand-back
+      // of a deep ring's stages b8 415 us.  A k-tile of a stage-4 3 x 3 takes
+      // ~0.12 us; its first loads, launch and stores, ~5 us, are the rest).
+      bf16x8_t fa[2][KS], fb[2][KS];
+      int cs = 0;  // stage of the k-tile read next
+      auto load = [&](auto bc) {
+        constexpr int buf = decltype(bc)::value;
+        const uint16_t *S = smem + cs * SM::kStage;
+        cs = cs + 1 == STAGES ? 0 : cs + 1;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const int ch = ((2 * ks + lh) ^ sw) * 8;
+          fa[buf][ks] = *reinterpret_cast<const bf16x8_t *>(S + aoff[0] + ch);
+          fb[buf][ks] = *reinterpret_cast<const bf16x8_t *>(S + boff[0] + ch);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      auto compute = [&](auto bc, int kt) {
+        constexpr int buf = decltype(bc)::value;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          bf16x8_t af = fa[buf][ks];
+          if constexpr (PRE) {
+            const float *ps = pre_s + kt * BK + (2 * ks + lh) * 8;
+            af = preact8(af, *reinterpret_cast<const float4 *>(ps), *reinterpret_cast<const float4 *>(ps + 4),
+                         *reinterpret_cast<const float4 *>(ps + kPreMax),
+                         *reinterpret_cast<const float4 *>(ps + kPreMax + 4));
+          }
+          acc[0][0] = EPI ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[buf][ks], af, acc[0][0], 0, 0, 0)
+                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, fb[buf][ks], acc[0][0], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      // A k-tile's barrier also hands the previous one's stage back to the
+      // producers, so this wave's reads of that stage must have returned.
+      auto next = [&] {
+        if constexpr (!LATE) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        else asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      };
+      using B0 = std::integral_constant<int, 0>;
+      using B1 = std::integral_constant<int, 1>;
+      next();
+      load(B0{});
+      for (int kt = 0; kt < nk; kt += 2) {
+        if (kt + 1 < nk) {
+          next();
+          load(B1{});
+        }
+        compute(B0{}, kt);
+        if (kt + 1 >= nk) break;
+        if (kt + 2 < nk) {
+          next();
+          load(B0{});
+        }
+        compute(B1{}, kt + 1);
+      }
+    } else {
     bf16x8_t af[2][TM], bfr[2][TN];
     auto read_frags = [&](const uint16_t *S, int ks, int buf, int kt) {
       const int ch = ((2 * ks + lh) ^ sw) * 8;
@@ -911,9 +981,11 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
         for (int i = 0; i < TM; ++i) af[buf][i] = preact8(af[buf][i], s0, s1, h0, h1);
       }
     };
+    int cs = 0;  // stage of k-tile kt
     for (int kt = 0; kt < nk; ++kt) {
       __builtin_amdgcn_s_barrier();
-      const uint16_t *S = smem + (kt % STAGES) * SM::kStage;
+      const uint16_t *S = smem + cs * SM::kStage;
+      cs = cs + 1 == STAGES ? 0 : cs + 1;
       read_frags(S, 0, 0, kt);
       __builtin_amdgcn_sched_barrier(0);
       static_for<KS>([&](auto ksc) {
@@ -929,6 +1001,7 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
         sched_step<0, TM * TN, (ks + 1 < KS) ? TM + TN : 0, 0>();
         __builtin_amdgcn_sched_barrier(0);
       });
+    }
     }
   }
 
@@ -1795,13 +1868,12 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
     //   M = 12544: 196 tiles) 256 x 128 stays faster, 60 against 73 us, and
     //   with two partitions in flight the larger tiles win throughout
     //   (ResNet-50 b256: 70.1k against 67.2k img/s).
-    // - 3 x 3 reductions of K >= 2048 with at most half as many 64 x 64 tiles
-    //   as CUs: 32 x 64 tiles, four stages, so twice the CUs walk the long
-    //   k-chain (ResNet-50 b8 stage-3 3 x 3 11.3 -> 10.3 us, stage 4
-    //   18.9 -> 16.7 us; with more tiles, as at b32, 64 x 64 stays faster);
-    if (a.lanes <= 1 && a.kh == 3 && a.K >= 2048 && a.N >= 64 &&
-        2 * (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) <= a.cus)
-      return launch_ws_ld<32, 64, 1, 2, 4, LD, 2, 2>(a, s);
+    // - at most half as many 64 x 64 tiles as CUs: 32 x 64 tiles, six stages,
+    //   so twice the CUs walk the k-chain (ResNet-50 b8 417 us against 422 us
+    //   with them on 3 x 3 layers only, ViT-B/16 b2 388 against 409 us; four
+    //   stages 425, eight 447 us).
+    if (a.lanes <= 1 && a.N >= 64 && 2 * (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) <= a.cus)
+      return launch_ws_ld<32, 64, 1, 2, 6, LD, 2, 2>(a, s);
     if (a.lanes <= 1 && a.N >= 64 && 2 * (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) < a.cus)
       return launch_ws_ld<64, 64, 2, 2, 4, LD, 2, 2>(a, s);
     if (a.lanes <= 1 && a.N >= 128 && a.K >= 1024 &&
@@ -1811,6 +1883,13 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
     // works on padding; 32 x 32 per consumer wave, three stages (DenseNet-121
     // b256: 56.8k -> 57.7k img/s against 256 x 32 tiles for large M and
     // 128 x 64 tiles, half of them padding, for small M).
+    // With at most half as many of them as CUs, 64 x 32 tiles (DenseNet-121
+    // b64 1,905 -> 1,798 us), with a quarter 32 x 32 (b16 1,190 -> 1,084 us
+    // against 1,105 us with 64 x 32), six stages.
+    if (a.N <= 32 && a.K >= 2 * BK && 4 * (int64_t)((a.M + 127) / 128) <= a.cus)
+      return launch_ws_ld<32, 32, 1, 1, 6, LD, 2, 2>(a, s);
+    if (a.N <= 32 && a.K >= 2 * BK && 2 * (int64_t)((a.M + 127) / 128) <= a.cus)
+      return launch_ws_ld<64, 32, 2, 1, 6, LD, 2, 2>(a, s);
     if (a.N <= 32 && a.K >= 2 * BK) return launch_ws_ld<128, 32, 4, 1, 3, LD, 2, 2>(a, s);
     if (a.N <= 64) {
       if (a.K >= 512 || a.K == BK) return launch_ws_ld<128, 64, 2, 2, 3, LD, 2, 2>(a, s);
@@ -1894,6 +1973,12 @@ hipError_t launch_conv_bf16(const ConvArgs &a, Loader ld, hipStream_t s) {
     // zero scale and shift turn into zeros.
     if (a.Kp >= 2 * BK && (a.lda ? a.lda : a.K) >= a.Kp &&
         (int64_t)a.M * (a.lda ? a.lda : a.K) * 2 < ((int64_t)1 << 31)) {
+      // Fewer 256 x 128 tiles, over all partitions in flight, than half the
+      // CUs: 64 x 64 tiles, four stages (DenseNet-121 b16 1,668 -> 1,190 us,
+      // b64 2,262 -> 1,905 us, b128 2,719 -> 2,367 us; with 196 tiles, as in the
+      // first block at b16, the large tiles stay faster, 217 against 232 us).
+      if (2 * a.lanes * (int64_t)((a.M + 255) / 256) * ((a.N + 127) / 128) <= a.cus)
+        return launch_ws_cfg<64, 64, 2, 2, 4, LD_GEMM, 1, 2, 2, true>(a, s);
       // Persistent 256 x 128 tiles, two stages (the scale and shift take
       // the LDS of a third): DenseNet-121 b256 56.7k -> 57.9k img/s against
       // the warp-specialised 128 x 128 tiles; 128 x 128 persistent tiles
