@@ -19,25 +19,30 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
 
 __device__ __forceinline__ float bf2f(uint16_t u) { return __uint_as_float((uint32_t)u << 16); }
 
-// erf by Abramowitz & Stegun, Handbook of Mathematical Functions, 7.1.26:
-// erf(x) = 1 - t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) exp(-x^2), t = 1 / (1 + p x)
-// for x >= 0 (odd extension), absolute error <= 1.5e-7: branch-free, one
-// reciprocal and one exponential, against a piecewise library erf.
-__device__ __forceinline__ float erf_as(float x) {
-  const float ax = fabsf(x);
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, ax, 1.0f));
-  float q = fmaf(t, 1.061405429f, -1.453152027f);
-  q = fmaf(t, q, 1.421413741f);
-  q = fmaf(t, q, -0.284496736f);
-  q = fmaf(t, q, 0.254829592f);
-  const float y = fmaf(-t * q, __builtin_amdgcn_exp2f(-ax * ax * 1.4426950408889634f), 1.0f);
-  return copysignf(y, x);
+// GELU in its exact (erf) form, v Phi(v) = max(v, 0) - |v| Phi(-|v|).  log2 Phi(-a)
+// is nearly quadratic: a polynomial of degree 8, fitted to it on [0, 6.5] for the
+// least maximum error of a Phi(-a) (weighted least squares, reweighted to the
+// minimax), and one exp2.  Past 6.5 the polynomial falls monotonically
+// (-35 at 6.5, -3160 at 16), so no clamp is needed there; |v| = inf is clamped
+// where it would meet exp2(-inf) = 0, and NaN goes through the polynomial.
+// Against float64 over [-40, 40]: 2.5e-7 at most, 3.5e-8 rms (erf by Abramowitz &
+// Stegun 7.1.26 with its reciprocal: 4.7e-7, 7.1e-8).
+__device__ __forceinline__ float gelu_erf(float v) {
+  const float a = fabsf(v);
+  float p = fmaf(a, -1.9919600617868127e-06f, 2.9272845495142974e-05f);
+  p = fmaf(a, p, -1.3809293159283698e-04f);
+  p = fmaf(a, p, -2.5342297158204019e-04f);
+  p = fmaf(a, p, 7.2163678705692291e-03f);
+  p = fmaf(a, p, -5.2603028714656830e-02f);
+  p = fmaf(a, p, -4.5917221903800964e-01f);
+  p = fmaf(a, p, -1.1511096954345703e+00f);
+  p = fmaf(a, p, -9.9999988079071045e-01f);
+  return fmaf(-fminf(a, 16.0f), __builtin_amdgcn_exp2f(p), fmaxf(v, 0.0f));
 }
 
-// GELU is the exact (erf) form: v * Phi(v) = 0.5 v (1 + erf(v / sqrt 2)).
 __device__ __forceinline__ float epilogue_act(float v, int relu, int gelu) {
   if (relu) v = fmaxf(v, 0.0f);
-  if (gelu) v = 0.5f * v * (1.0f + erf_as(v * 0.70710678118654752f));
+  if (gelu) v = gelu_erf(v);
   return v;
 }
 
