@@ -1859,9 +1859,11 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
     if (LD == LD_S2D) return launch_ws_ld<128, 64, 2, 2, 3, LD, 2, 2>(a, s);
     // With one partition in flight (none other fills the CUs this launch
     // leaves idle):
-    // - fewer 128 x 128 tiles than half the CUs: 64 x 64 tiles, four stages
+    // - fewer 128 x 128 tiles than 5/8 of the CUs: 64 x 64 tiles, four stages
     //   (ResNet-50 b8: 706 -> 528 us of convolutions per pass; b32 stage-4
-    //   3 x 3s 30 -> 20 us);
+    //   3 x 3s 30 -> 20 us; at 147 to 150 tiles, ResNet-18 b24's stage 2 and
+    //   ViT-B/16 b16's projections, 211 -> 201 and 956 -> 934 us in all; at 196,
+    //   ResNet-18 b64's stage 3, 326 -> 339 us, so not there);
     // - long reductions with fewer 256-row tiles than half the CUs:
     //   persistent 128 x 128 tiles (ResNet-18 b64 stage 3: 111 -> 82 us,
     //   ResNet-50 b32 31.8k -> 37.4k img/s).  With more (ResNet-50 stage 4 at
@@ -1874,7 +1876,7 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
     //   stages 425, eight 447 us).
     if (a.lanes <= 1 && a.N >= 64 && 2 * (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) <= a.cus)
       return launch_ws_ld<32, 64, 1, 2, 6, LD, 2, 2>(a, s);
-    if (a.lanes <= 1 && a.N >= 64 && 2 * (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) < a.cus)
+    if (a.lanes <= 1 && a.N >= 64 && 8 * (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) < 5 * (int64_t)a.cus)
       return launch_ws_ld<64, 64, 2, 2, 4, LD, 2, 2>(a, s);
     if (a.lanes <= 1 && a.N >= 128 && a.K >= 1024 &&
         2 * (int64_t)((a.M + 255) / 256) * ((a.N + 127) / 128) < a.cus)
@@ -1903,9 +1905,12 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
       return launch_pws_ld<128, 256, 2, 4, 4, 3, LD, 2>(a, s);
     } else if (a.N <= 128) {
       if (a.kh == 1 && a.K <= 256 && a.K >= 2 * BK) return launch_pws_ld<256, 128, 4, 2, 4, 3, LD, 2>(a, s);
-      // 3 x 3 over 64 channels to 128 (VGG conv2_1): persistent 256 x 128
-      // tiles (VGG-16 b128 +1.6%)
-      if (a.kh == 3 && a.K <= 9 * 64 && a.K >= 2 * BK) return launch_pws_ld<256, 128, 4, 2, 4, 3, LD, 2>(a, s);
+      // 3 x 3 over 64 channels to 128 (VGG conv2_1), or any with a 256 x 128 tile
+      // per CU: those on the persistent kernel (VGG-16 b128 +1.6%; VGG-16 b37 to
+      // pool3 899 -> 887 us, ResNet-50 b256 3,211 -> 3,192 us; with 196
+      // tiles, ResNet-18 b64's stage 2, 326 -> 329 us, so not there)
+      if (a.kh == 3 && a.K >= 2 * BK && (a.K <= 9 * 64 || (a.M + 255) / 256 >= a.cus))
+        return launch_pws_ld<256, 128, 4, 2, 4, 3, LD, 2>(a, s);
       // 1 x 1 with K >= 512 (ResNet-50 stage-2 reductions): with partitions
       // in flight persistent 256 x 128 tiles (b256 +1.0%, b512 +0.8%), alone
       // the latency-bound three-workgroups-per-CU tiles
