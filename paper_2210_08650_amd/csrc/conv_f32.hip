@@ -9,7 +9,7 @@ namespace hapi {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int BKF = 16;        // k-tile (fp32 elements)
+constexpr int BKF = kF32Tile;  // k-tile (fp32 elements)
 constexpr int LDSF = BKF + 4;  // LDS row pitch in floats (80 B)
 
 template <int LD>
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void conv_f32_kernel(ConvArgs a) {
 
 
 // The register-staged kernel above takes what the DMA kernel's 31-bit byte
-// offsets and tap table cannot address (dma_fits).
+// offsets and tap table cannot address (f32_dma_fits).
 
 // ------------------------------------------------------- LDS-DMA pipeline
 
@@ -224,8 +224,6 @@ __device__ __forceinline__ void dma4(u32x4_t srd, uint32_t lds, uint32_t voff) {
       : "memory");
 }
 
-constexpr int kTapMax = 1024;  // padded K of the element-gather loader's table
-
 // fp32 MFMAs are slow (64 clocks for 4096 FLOP), so the matrix pipe bounds this
 // once it never waits: tiles go by DMA into an ST-stage ring, and each half of
 // a wave's fragments is read into the registers that the MFMAs just issued
@@ -253,7 +251,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_f32_dma_kernel(ConvArgs a) {
   constexpr int kA = BM / 4 * kGroup, kStage = kA + BN * 64;
   static_assert((ST - 2) * NQ < 64 && TM >= 1 && TN >= 1, "tile");
   __shared__ __attribute__((aligned(1024))) uint8_t smem[ST * kStage];
-  __shared__ __attribute__((aligned(16))) int2 taps[GATHER ? kTapMax : 1];
+  __shared__ __attribute__((aligned(16))) int2 taps[GATHER ? kF32Taps : 1];
 
   const int tiles_n = (a.N + BN - 1) / BN;
   const int tile = a.rev ? (int)gridDim.x - 1 - xcd_remap(blockIdx.x, gridDim.x) : xcd_remap(blockIdx.x, gridDim.x);
@@ -508,15 +506,6 @@ hipError_t launch_dma_cfg(const ConvArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The DMA kernel forms 31-bit byte offsets, and its gather a table of Kp taps.
-bool dma_fits(const ConvArgs &a, Loader ld) {
-  const int64_t lim = (int64_t)1 << 31;
-  if ((int64_t)a.n_img * a.H * a.W * a.C * 4 >= lim || (int64_t)a.N * a.Kp * 4 >= lim) return false;
-  if (a.H >= 0x3000 || a.W >= 0x3000 || a.pad >= 0x1000) return false;  // tap rows of 0x4000 lie outside every image
-  if (ld == LD_NCHW) return a.Kp <= kTapMax;
-  return a.C % BKF == 0 && a.Kp == a.K;
-}
-
 template <int LD>
 hipError_t launch_f32_ld(const ConvArgs &a, hipStream_t s) {
   if (!f32_seq(a, (Loader)LD)) {
@@ -533,16 +522,6 @@ hipError_t launch_f32_ld(const ConvArgs &a, hipStream_t s) {
 
 }  // namespace
 
-// Below three 64 x 64 tiles per CU the slices run apart, as 6 to 16 times as many
-// workgroups: AlexNet b16 297 us against 355 us with all slices in one
-// workgroup from one tile per CU on, b64 894 against 945 us; above, the partial
-// sums' traffic and the reduction's launch cost more (b128 1,574 us against
-// 1,785 us with every layer split).  The sums are the same either way.
-bool f32_seq(const ConvArgs &a, Loader ld) {
-  if (a.splits <= 1) return true;
-  return dma_fits(a, ld) && (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 3 * (int64_t)a.cus;
-}
-
 hipError_t launch_f32_split_reduce(const ConvArgs &a, hipStream_t s) {
   if (a.splits <= 1 || !a.part || a.N % 4 != 0) return hipErrorInvalidValue;
   const int64_t items = (int64_t)a.M * (a.N / 4);
@@ -551,7 +530,7 @@ hipError_t launch_f32_split_reduce(const ConvArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_conv_f32(const ConvArgs &a, Loader ld, hipStream_t s) {
-  const bool dma = dma_fits(a, ld);
+  const bool dma = f32_dma_fits(a, ld);
   switch (ld) {
     case LD_NHWC:
     case LD_GEMM:

@@ -139,9 +139,27 @@ hipError_t launch_conv_f32(const ConvArgs &a, Loader ld, hipStream_t s);
 // nothing, when conv_pp_supported says no.
 bool conv_pp_supported(const ConvArgs &a, Loader ld);
 hipError_t launch_conv_pp(const ConvArgs &a, Loader ld, hipStream_t s);
+constexpr int kF32Tile = 16;    // k-tile of the fp32 convolutions
+constexpr int kF32Taps = 1024;  // padded K of their element-gather loader's table
+// The fp32 DMA kernel forms 31-bit byte offsets, and its gather a table of Kp taps.
+inline bool f32_dma_fits(const ConvArgs &a, Loader ld) {
+  const int64_t lim = (int64_t)1 << 31;
+  if ((int64_t)a.n_img * a.H * a.W * a.C * 4 >= lim || (int64_t)a.N * a.Kp * 4 >= lim) return false;
+  if (a.H >= 0x3000 || a.W >= 0x3000 || a.pad >= 0x1000) return false;  // tap rows of 0x4000 lie outside every image
+  if (ld == LD_NCHW) return a.Kp <= kF32Taps;
+  return a.C % kF32Tile == 0 && a.Kp == a.K;
+}
 // Whether launch_conv_f32 sums the slices itself (no partial sums, so no
 // launch_f32_split_reduce): a single slice, or enough tiles without them.
-bool f32_seq(const ConvArgs &a, Loader ld);
+// Below three 64 x 64 tiles per CU the slices run apart, as 6 to 16 times as many
+// workgroups: AlexNet b16 297 us against 355 us with all slices in one
+// workgroup from one tile per CU on, b64 894 against 945 us; above, the partial
+// sums' traffic and the reduction's launch cost more (b128 1,574 us against
+// 1,785 us with every layer split).  The sums are the same either way.
+inline bool f32_seq(const ConvArgs &a, Loader ld) {
+  if (a.splits <= 1) return true;
+  return f32_dma_fits(a, ld) && (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 3 * (int64_t)a.cus;
+}
 // The ordered sum of an fp32 convolution's slices (!f32_seq), then its bias,
 // residual and activation, into a.y.
 hipError_t launch_f32_split_reduce(const ConvArgs &a, hipStream_t s);
