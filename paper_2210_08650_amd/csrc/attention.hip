@@ -142,16 +142,16 @@ __global__ __launch_bounds__(64 * kAttnWaves, 1) void attention_kernel(const uin
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[tt][r]);
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      // exp2((s - mx) scale) as one multiply-add: the rounding of mx scale is
-      // common to all of a query's terms and cancels in the division.
-      const float mxs = mx * scale_log2;
       float sum = 0.0f;
 #pragma unroll
       for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          // arguments are <= 0 (up to rounding): the hardware exp2 (v_exp_f32) is exact enough
-          const float pr = __builtin_amdgcn_exp2f(fmaf(s[tt][r], scale_log2, -mxs));
+          // arguments are <= 0: the hardware exp2 (v_exp_f32) is exact enough.  The
+          // difference comes first: s scale - mx scale as one multiply-add keeps the
+          // rounding of mx scale, which from scores of about 1e10 on leaves the
+          // exponent's range (a row of NaN).
+          const float pr = __builtin_amdgcn_exp2f((s[tt][r] - mx) * scale_log2);
           s[tt][r] = pr;
           sum += pr;
         }
