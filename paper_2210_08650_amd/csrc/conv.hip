@@ -1819,21 +1819,48 @@ hipError_t launch_nchw_out(const ConvArgs &a, hipStream_t s) {
   return launch_ws_ld<128, 128, 2, 2, 2, LD, 0, 2>(a, s);
 }
 
+// Whether 256 x 256 tiles (conv_pp.hip) finish before the kernels that
+// launch_pipe_ld takes otherwise.  Both run in rounds over the CUs, so what counts
+// is r rounds of 256 x 256 tiles against ro of tiles half that size (128 x 256,
+// 256 x 128, or two of 128 x 128), each 0.55 to 0.6 of a large one's time: r < 0.6 ro
+// (launches of one layer back to back, 256 x 256 tiles against the other kernel;
+// 3 x 3 over 256 channels: 147 tiles, r = 1 and ro = 2, 56 against 62 us; 294, 2
+// and 3, 114 against 101; 441, 2 and 4, 122 against 132; 588, 3 and 5, 180 against
+// 171; residual 3,072 -> 768: 270 tiles, 2 and 3, 139 against 129).  The short
+// launches of 1 x 1s under K = 512 need 0.57 (128 -> 256: 780 tiles, 4 and 7, 46.0
+// against 42.0 us).  Other kernels' rounds grow longer as they fill, so there
+// the large tiles win from a part g of their own rounds filled on:
+// - 9/16 for wide linear layers and fused shortcuts (ViT-B/16's fc1 at 28
+//   images, 264 of 512, 52.6 against 50.3 us; b32, 300 tiles, 1,287 against 1,291 us
+//   in all; shortcuts: 264 tiles 47.4 against 46.5 us, 314 tiles 32.6 against 37.2);
+// - 10/16 for long reductions (512 channels: 294 of 512 207 against 197 us,
+//   356 216 against 214, 380 223 against 227; VGG-16 b56, 344 tiles, 1,786 us in
+//   all against 1,817);
+// - 8/16 for other 1 x 1s over 512 channels and more (270 of 512 37.3 against 37.9 us).
+// Residual layers of 1,024 and more channels otherwise run on small tiles, three
+// workgroups per CU, which only rounds filled to 3/4 beat (K = 512: 296 of 512
+// tiles 42.4 against 39.9 us, 392 47.9 against 50.8), or to 7/8 with a short
+// reduction and one partition (K = 256: 392 of 512 tiles 37.9 against 36.3 us, 196
+// of 256 20.3 against 21.5; ResNet-50 b256 from stage 2, two partitions of 392
+// tiles, 1,531 against 1,562 us in all).  With several partitions in flight the
+// others fill the last of several rounds (ViT-B/16 b152, qkv in three rounds:
+// 4,473 us with these tiles, 4,592 us without).  A last column tile that is
+// mostly padding (N = 320) stays on narrower tiles.
+inline bool pp_pays(const ConvArgs &a, Loader ld) {
+  if (a.N % 256 != 0 && a.N < 1024) return false;
+  const int64_t cus = a.cus > 0 ? a.cus : cu_count(), cols = (a.N + 255) / 256;
+  const int64_t t = (a.M + 255) / 256 * cols, r = (t + cus - 1) / cus, ro = ((a.M + 127) / 128 * cols + cus - 1) / cus;
+  if (a.lanes > 1 && r > 2) return true;
+  if (a.res && a.N >= 1024) return 8 * t > (a.K < 512 && r > 1 && a.lanes <= 1 ? 7 : 6) * cus * r;
+  const bool wide = ld == LD_GEMM && a.N >= 2048 && a.K <= 1024;
+  const int f = ld != LD_CAT && a.kh == 1 && a.K < 512 ? 57 : 60;
+  const int g = a.res ? 16 : wide || ld == LD_CAT ? 9 : a.N < 512 ? 16 : a.K >= 2048 ? 10 : a.kh == 1 && a.K >= 512 ? 8 : 16;
+  return 100 * r < f * ro || 16 * t > g * cus * r;
+}
+
 template <int LD>
 hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
   if (a.out_hw > 0) return launch_nchw_out<LD>(a, s);
-  // 256 x 256 tiles (conv_pp.hip) once they cover more than half the CUs: a
-  // 128 x 256 tile of the persistent kernel takes ~0.65 of the time of a
-  // 256 x 256 tile here, so with fewer tiles the smaller ones finish first in
-  // one round (ViT-B/16 block at 48 images, 111 tiles for the projections:
-  // 258 against 238 us with them on 128 x 128 tiles), with more they need
-  // two (ViT-B/16 b128, 150 tiles per partition: 3,827 against 4,143 us;
-  // VGG-16 b128 4,143 -> 3,984 us; ResNet-50 b256 3,396 -> 3,297 us).  A
-  // last column tile that is mostly padding (N = 320) stays on narrower tiles.
-  if constexpr (LD == LD_GEMM || LD == LD_NHWC || LD == LD_CAT)
-    if ((a.N % 256 == 0 || a.N >= 1024) &&
-        2 * (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) > a.cus && conv_pp_supported(a, (Loader)LD))
-      return launch_conv_pp(a, (Loader)LD, s);
   // Measured on MI355X over the ResNet-50 conv shapes (per-layer kernel
   // traces of every configuration above):
   // - the warp-specialised kernel with two workgroups per CU (128 x 64 tiles)
@@ -1855,6 +1882,8 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
   // per CU (short-K kernel).
   if (LD == LD_GEMM && a.Kp == BK && a.N <= 64 && !a.res) return launch_short_ld<128, 64, 2, 2, LD, 3>(a, s);
   if (LD == LD_GEMM && a.Kp == 2 * BK && a.N == 512 && a.res) return launch_short_ld<128, 64, 2, 2, LD, 3>(a, s);
+  if constexpr (LD == LD_GEMM || LD == LD_NHWC || LD == LD_CAT)
+    if (pp_pays(a, (Loader)LD) && conv_pp_supported(a, (Loader)LD)) return launch_conv_pp(a, (Loader)LD, s);
   if (ws_eligible(a, (Loader)LD)) {
     if (LD == LD_S2D) return launch_ws_ld<128, 64, 2, 2, 3, LD, 2, 2>(a, s);
     // With one partition in flight (none other fills the CUs this launch

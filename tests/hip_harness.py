@@ -63,6 +63,39 @@ class Guarded:
                              f"of a {self.nbytes}-byte buffer"
 
 
+def kernel_names(call):
+    """Names of the library's kernels that ``call`` launches, e.g.
+    ``conv_bf16_ws2_kernel<64, 64, 2, 2, 4, 1, 1, 2, false>``, in launch order."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+        call()
+        torch.cuda.synchronize()
+    names = []
+    for e in sorted(p.events(), key=lambda e: e.time_range.start):
+        if "hapi::" in e.name:
+            n = e.name.removeprefix("void ").replace("hapi::", "").replace("(anonymous namespace)::", "")
+            names.append(n.replace("(Loader)", "").split("(")[0])
+    return names
+
+
+def assert_routes(call, wanted=(), unwanted=()):
+    """``call`` launches a kernel whose name starts with each of ``wanted`` and none
+    that starts with one of ``unwanted``.  The tile rules count tiles against CUs,
+    so this holds for the 256-CU device the cases are made for.  The tracer can drop
+    records: three tries for it to see them all."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        return
+    for _ in range(3):
+        names = kernel_names(call)
+        bad = [n for n in names if any(n.startswith(u) for u in unwanted)]
+        missing = [w for w in wanted if not any(n.startswith(w) for n in names)]
+        assert not bad, (bad, names)
+        if names and not missing:
+            return
+    raise AssertionError(f"kernels {missing} not among {names}")
+
+
 class Runner:
     """A packed model resident on the GPU, ready for repeated extraction."""
 

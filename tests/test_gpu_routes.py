@@ -1,0 +1,54 @@
+"""Which tiles the bf16 convolutions run on, on a 256-CU device.
+
+Results do not depend on the tiles (test_gpu_large_tiles and test_gpu_small_tiles
+compare them bit for bit); times do: a route taken at a size where another kernel is
+faster is the fault these cases pin.  Sizes lie on both sides of each rule.
+"""
+import pytest
+
+import paper_2210_08650_amd as H
+from paper_2210_08650_amd import models as PM
+import synth
+from tests.hip_harness import Runner, assert_routes, images_for
+
+pytestmark = pytest.mark.gpu
+
+POOL1 = PM.maxpool(1, 1)
+PP = "conv_bf16_pp_kernel"
+
+
+def _conv(cin, cout, k, hw, batch, inflight=1):
+    # the second convolution takes the split
+    return [POOL1, PM.conv(cin, cout, k, 1, k // 2), PM.conv(cout, 64, 1)], (cin, hw, hw), batch, inflight, 3
+
+
+def _expansion(width, hw, batch, inflight=1):
+    block = dict(kind=H.HAPI_BOTTLENECK, cin=4 * width, width=width, cout=4 * width, stride=1)
+    return [POOL1, block, PM.conv(4 * width, 64, 1)], (4 * width, hw, hw), batch, inflight, 3
+
+
+# (what, kernels to see, kernels not to see)
+CASES = {
+    # 256 x 256 tiles: one round of 147, two rounds for 294 (three halves are faster),
+    # two for 441 (four halves)
+    "3x3 147 tiles": (_conv(128, 256, 3, 56, 12), [PP], []),
+    "3x3 294 tiles": (_conv(128, 256, 3, 56, 24), [], [PP]),
+    "3x3 441 tiles": (_conv(128, 256, 3, 56, 36), [PP], []),
+    # a residual short reduction: rounds filled to 148, 196 of 256 and 296 of 512
+    "expansion 148 tiles": (_expansion(256, 14, 48), [], [PP]),
+    "expansion 196 tiles": (_expansion(256, 14, 64), [PP + "<1, 1, 3>"], []),
+    "expansion 296 tiles": (_expansion(256, 14, 96), [], [PP + "<1, 1, 3>"]),
+    # the two-k-tile residual expansion has a kernel of its own at every size
+    "short expansion": (_expansion(128, 28, 64), ["conv_bf16_short_kernel"], [PP + "<1, 1, 3>"]),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_route(name):
+    (layers, in_shape, batch, inflight, split), wanted, unwanted = CASES[name]
+    raw = synth.params(15, PM.raw_manifest(layers, in_shape))
+    print(f"case {name}", flush=True)
+    r = Runner(layers, H.HAPI_BF16, raw, in_shape)
+    xd, _ = images_for(H.HAPI_BF16, synth.images(15, 1, *in_shape))
+    xd = xd.expand(batch, *in_shape).contiguous()
+    assert_routes(lambda: r.extract(xd, split, inflight=inflight, chunk=-(-batch // inflight)), wanted, unwanted)
