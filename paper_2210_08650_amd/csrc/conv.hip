@@ -1888,11 +1888,17 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
     if (LD == LD_S2D) return launch_ws_ld<128, 64, 2, 2, 3, LD, 2, 2>(a, s);
     // With one partition in flight (none other fills the CUs this launch
     // leaves idle):
-    // - fewer 128 x 128 tiles than 5/8 of the CUs: 64 x 64 tiles, four stages
-    //   (ResNet-50 b8: 706 -> 528 us of convolutions per pass; b32 stage-4
-    //   3 x 3s 30 -> 20 us; at 147 to 150 tiles, ResNet-18 b24's stage 2 and
-    //   ViT-B/16 b16's projections, 211 -> 201 and 956 -> 934 us in all; at 196,
-    //   ResNet-18 b64's stage 3, 326 -> 339 us, so not there);
+    // - fewer 128 x 128 tiles than half the CUs, or than 5/8 for reductions under
+    //   20 k-tiles: 64 x 64 tiles, four stages (ResNet-50 b8: 706 -> 528 us of
+    //   convolutions per pass; b32 stage-4 3 x 3s 30 -> 20 us; at 147 to 150
+    //   tiles 64 -> 128-channel 3 x 3s 17.0 -> 13.2 us, 256 -> 128 1 x 1s
+    //   10.2 -> 8.8 us, 768 -> 768 14.9 -> 13.6 us, and in whole passes
+    //   ResNet-18 b24 (K = 576 to 1,216) 218 -> 212 us, ResNet-50 b48 (K = 1,024)
+    //   979 -> 976 us).  For longer ones the persistent 128 x 128 tiles
+    //   below are faster at that count (3 x 3s of K = 2,304 and 4,608 21.3 and
+    //   30.1 us against 23.1 and 39.9 us; 3,072 -> 768 1 x 1s 23.8 against 29.4
+    //   us), and for 128-channel 1 x 1s of K >= 512 three workgroups per CU
+    //   (9.0 against 10.2 us);
     // - long reductions with fewer 256-row tiles than half the CUs:
     //   persistent 128 x 128 tiles (ResNet-18 b64 stage 3: 111 -> 82 us,
     //   ResNet-50 b32 31.8k -> 37.4k img/s).  With more (ResNet-50 stage 4 at
@@ -1905,7 +1911,9 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
     //   stages 425, eight 447 us).
     if (a.lanes <= 1 && a.N >= 64 && 2 * (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) <= a.cus)
       return launch_ws_ld<32, 64, 1, 2, 6, LD, 2, 2>(a, s);
-    if (a.lanes <= 1 && a.N >= 64 && 8 * (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) < 5 * (int64_t)a.cus)
+    const bool short_k = a.K < 20 * BK && !(a.kh == 1 && a.N <= 128 && a.K >= 512);
+    if (a.lanes <= 1 && a.N >= 64 &&
+        8 * (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) < (short_k ? 5 : 4) * (int64_t)a.cus)
       return launch_ws_ld<64, 64, 2, 2, 4, LD, 2, 2>(a, s);
     if (a.lanes <= 1 && a.N >= 128 && a.K >= 1024 &&
         2 * (int64_t)((a.M + 255) / 256) * ((a.N + 127) / 128) < a.cus)

@@ -15,6 +15,9 @@ pytestmark = pytest.mark.gpu
 
 POOL1 = PM.maxpool(1, 1)
 PP = "conv_bf16_pp_kernel"
+# 64 x 64 tiles stored as NHWC (the split layer's go to NCHW): 3 x 3 and 1 x 1
+W64 = "conv_bf16_ws2_kernel<64, 64, 2, 2, 4, 0, 3, 2"
+W64L = "conv_bf16_ws2_kernel<64, 64, 2, 2, 4, 1, 1, 2"
 
 
 def _conv(cin, cout, k, hw, batch, inflight=1):
@@ -40,6 +43,11 @@ CASES = {
     "expansion 296 tiles": (_expansion(256, 14, 96), [], [PP + "<1, 1, 3>"]),
     # the two-k-tile residual expansion has a kernel of its own at every size
     "short expansion": (_expansion(128, 28, 64), ["conv_bf16_short_kernel"], [PP + "<1, 1, 3>"]),
+    # 148 tiles of 128 x 128 on 256 CUs: 64 x 64 tiles only for short reductions
+    "3x3 of 9 k-tiles": (_conv(64, 128, 3, 28, 24), [W64], []),
+    "3x3 of 36 k-tiles": (_conv(256, 256, 3, 14, 48), ["conv_bf16_pws_kernel<128, 128"], [W64]),
+    "1x1 of 12 k-tiles": (_conv(768, 768, 1, 14, 16), [W64L], []),
+    "1x1 of 48 k-tiles": (_conv(3072, 768, 1, 14, 16), ["conv_bf16_pws_kernel<128, 128"], [W64L]),
 }
 
 
