@@ -18,6 +18,7 @@ PP = "conv_bf16_pp_kernel"
 # 64 x 64 tiles stored as NHWC (the split layer's go to NCHW): 3 x 3 and 1 x 1
 W64 = "conv_bf16_ws2_kernel<64, 64, 2, 2, 4, 0, 3, 2"
 W64L = "conv_bf16_ws2_kernel<64, 64, 2, 2, 4, 1, 1, 2"
+TALL = "conv_bf16_pws_kernel<256, 128"
 
 
 def _conv(cin, cout, k, hw, batch, inflight=1):
@@ -48,6 +49,10 @@ CASES = {
     "3x3 of 36 k-tiles": (_conv(256, 256, 3, 14, 48), ["conv_bf16_pws_kernel<128, 128"], [W64]),
     "1x1 of 12 k-tiles": (_conv(768, 768, 1, 14, 16), [W64L], []),
     "1x1 of 48 k-tiles": (_conv(3072, 768, 1, 14, 16), ["conv_bf16_pws_kernel<128, 128"], [W64L]),
+    # 128-channel 3 x 3s: the persistent kernel from a round and a half of 256-row tiles on
+    "3x3 to 128, 294 tiles": (_conv(128, 128, 3, 56, 24), [], [TALL]),
+    "3x3 to 128, 392 tiles": (_conv(128, 128, 3, 56, 32), [TALL], []),
+    "3x3 to 128, two partitions of 319": (_conv(128, 128, 3, 28, 208, 2), [], [TALL]),
 }
 
 
