@@ -189,41 +189,6 @@ __global__ __launch_bounds__(kThreads) void conv_f32_kernel(ConvArgs a) {
 
 // ------------------------------------------------------- LDS-DMA pipeline
 
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ u32x4_t make_srd(const void *p) {
-  const uint64_t v = (uint64_t)(uintptr_t)p;
-  u32x4_t r;
-  r[0] = (uint32_t)v;
-  r[1] = (uint32_t)(v >> 32) & 0xffffu;
-  r[2] = 0x7fffffffu;
-  r[3] = 0x00020000u;
-  return r;
-}
-
-// 16 or 4 bytes per lane from the buffer at voff + soff into LDS at
-// lds + 16 * lane or lds + 4 * lane; an offset voff >= 2^31 - 1 reads zeros.  In
-// asm because the compiler would otherwise wait for every DMA in flight
-// before each LDS read; the kernel places those waits itself.
-__device__ __forceinline__ void dma16(u32x4_t srd, uint32_t lds, uint32_t voff, uint32_t soff) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %1, %2, %3 offen lds"
-      :
-      : "s"(lds), "v"(voff), "s"(srd), "s"(soff)
-      : "memory");
-}
-__device__ __forceinline__ void dma4(u32x4_t srd, uint32_t lds, uint32_t voff) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dword %1, %2, 0 offen lds"
-      :
-      : "s"(lds), "v"(voff), "s"(srd)
-      : "memory");
-}
-
 // fp32 MFMAs are slow (64 clocks for 4096 FLOP), so the matrix pipe bounds this
 // once it never waits: tiles go by DMA into an ST-stage ring, and each half of
 // a wave's fragments is read into the registers that the MFMAs just issued
@@ -312,14 +277,14 @@ __global__ __launch_bounds__(kThreads, 2) void conv_f32_dma_kernel(ConvArgs a) {
 #pragma unroll
       for (int i = 0; i < NA; ++i) {
         const bool ok = (unsigned)(rhi[i] + u) < (unsigned)a.H && (unsigned)(rwi[i] + v) < (unsigned)a.W;
-        dma4(srd_a, st + (wave * NA + i) * kGroup, ok ? (uint32_t)(rbase[i] + tp.x) : kOob);
+        lds_dma4(srd_a, st + (wave * NA + i) * kGroup, ok ? (uint32_t)(rbase[i] + tp.x) : kOob);
       }
     } else {
       const int off = live ? ((s_kh * a.W + s_kw) * a.C + s_c) * 4 : 0, kh = live ? s_kh : 0x4000;
 #pragma unroll
       for (int i = 0; i < NA; ++i) {
         const bool ok = (unsigned)(rhi[i] + kh) < (unsigned)a.H && (unsigned)(rwi[i] + s_kw) < (unsigned)a.W;
-        dma16(srd_a, st + (wave * NA + i) * 1024, ok ? (uint32_t)(rbase[i] + off) : kOob, 0);
+        lds_dma16(srd_a, st + (wave * NA + i) * 1024, ok ? (uint32_t)(rbase[i] + off) : kOob, 0);
       }
       s_c += BKF;
       if (s_c == a.C) {
@@ -332,7 +297,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_f32_dma_kernel(ConvArgs a) {
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j)
-      dma16(srd_b, st + kA + (wave * NB + j) * 1024, live ? boff[j] : kOob, (uint32_t)(live ? s_kt * BKF * 4 : 0));
+      lds_dma16(srd_b, st + kA + (wave * NB + j) * 1024, live ? boff[j] : kOob, (uint32_t)(live ? s_kt * BKF * 4 : 0));
     ++s_kt;
     stage_w = stage_w + 1 == ST ? 0 : stage_w + 1;
   };

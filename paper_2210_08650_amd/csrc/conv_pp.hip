@@ -45,8 +45,6 @@ constexpr int kHalf = 128 * BK * 2;      // bytes of half an operand tile (128 r
 constexpr int kStage = 4 * kHalf;        // A halves 0, 1, then B halves 0, 1
 constexpr int kBiasMax = 4096;
 
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
 // n / d for n < 2^31 by one 64-bit multiply and shift.
 struct Magic {
   uint32_t mul;
@@ -64,30 +62,6 @@ struct PPArgs {
   ConvArgs a;
   Magic hw, w;  // divisors of the GEMM row: pixels (or pooling windows) per image and per row
 };
-
-__device__ __forceinline__ u32x4_t make_srd(const void *p) {
-  const uint64_t v = (uint64_t)(uintptr_t)p;
-  u32x4_t r;
-  r[0] = (uint32_t)v;
-  r[1] = (uint32_t)(v >> 32) & 0xffffu;
-  r[2] = 0x7fffffffu;
-  r[3] = 0x00020000u;
-  return r;
-}
-
-// 16 bytes per lane from the buffer at voff + soff into LDS at lds + 16 * lane;
-// an offset voff >= 2^31 - 1 reads zeros.  In asm because the compiler would
-// otherwise wait for every DMA in flight before each LDS read; the kernel
-// places those waits itself.  It has no register output.
-__device__ __forceinline__ void dma16(u32x4_t srd, uint32_t lds, uint32_t voff, uint32_t soff) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %1, %2, %3 offen lds"
-      :
-      : "s"(lds), "v"(voff), "s"(srd), "s"(soff)
-      : "memory");
-}
 
 // EK: epilogue of bias and ReLU (0), GELU (1), ReLU and 2 x 2 max pooling (2),
 // residual and ReLU (3).
@@ -188,19 +162,19 @@ __global__ __launch_bounds__(kWaves * 64, 1) void conv_bf16_pp_kernel(PPArgs pa)
       const uint32_t dst = lds0 + stage + h * kHalf + (wave * 2 + i) * 1024;
       const int x = 2 * h + i;
       if (LD == LD_GEMM) {
-        dma16(srd_a, dst, (uint32_t)aoff[x], (uint32_t)(s_kt * BK * 2));
+        lds_dma16(srd_a, dst, (uint32_t)aoff[x], (uint32_t)(s_kt * BK * 2));
       } else if (LD == LD_CAT && s_kt >= nk1) {
-        dma16(srd_a2, dst, (uint32_t)a2off[LD == LD_CAT ? x : 0], (uint32_t)((s_kt - nk1) * BK * 2));
+        lds_dma16(srd_a2, dst, (uint32_t)a2off[LD == LD_CAT ? x : 0], (uint32_t)((s_kt - nk1) * BK * 2));
       } else {
         const uint32_t v = (amask[x] >> s_tap) & 1u ? (uint32_t)(aoff[x] + s_tapoff) : kOob;
-        dma16(srd_a, dst, v, (uint32_t)(s_cb * BK * 2));
+        lds_dma16(srd_a, dst, v, (uint32_t)(s_cb * BK * 2));
       }
     }
   };
   auto issue_b = [&](uint32_t stage, int h) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      dma16(srd_b, lds0 + stage + (2 + h) * kHalf + (wave * 2 + i) * 1024, (uint32_t)boff[2 * h + i],
+      lds_dma16(srd_b, lds0 + stage + (2 + h) * kHalf + (wave * 2 + i) * 1024, (uint32_t)boff[2 * h + i],
             (uint32_t)(s_kt * BK * 2));
   };
 

@@ -59,6 +59,43 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 constexpr unsigned kOob = 0x80000000u;  // a byte offset outside every buffer range
 
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// A raw buffer of 2^31 - 1 bytes from p on.
+__device__ __forceinline__ u32x4_t make_srd(const void *p) {
+  const uint64_t v = (uint64_t)(uintptr_t)p;
+  u32x4_t r;
+  r[0] = (uint32_t)v;
+  r[1] = (uint32_t)(v >> 32) & 0xffffu;
+  r[2] = 0x7fffffffu;
+  r[3] = 0x00020000u;
+  return r;
+}
+
+// 16 or 4 bytes per lane from the buffer at voff + soff into LDS at
+// lds + 16 * lane or lds + 4 * lane; an offset voff >= 2^31 - 1 reads zeros.  In
+// asm because the compiler would otherwise wait for every DMA in flight
+// before each LDS read; the kernels place those waits themselves.  No register
+// output; m0 is reserved, and nothing else in those kernels uses it.
+__device__ __forceinline__ void lds_dma16(u32x4_t srd, uint32_t lds, uint32_t voff, uint32_t soff) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %1, %2, %3 offen lds"
+      :
+      : "s"(lds), "v"(voff), "s"(srd), "s"(soff)
+      : "memory");
+}
+__device__ __forceinline__ void lds_dma4(u32x4_t srd, uint32_t lds, uint32_t voff) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dword %1, %2, 0 offen lds"
+      :
+      : "s"(lds), "v"(voff), "s"(srd)
+      : "memory");
+}
+
 // Per-row state of the rows a thread gathers for the A tile.
 struct RowState {
   int base;  // element offset of the row's image (NHWC / NCHW) or of the row (GEMM)
