@@ -837,9 +837,11 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
       return (unsigned)((((int64_t)c * a.H + u0) * a.W) * 2);
     };
     int q = 0, qs = 0;  // next k-tile to issue, and its stage
-    // Before issuing k-tile q into stage q % STAGES: once STAGES - 1 tiles are
-    // in flight, wait until k-tile q - STAGES + 1 has landed, then meet the
-    // consumers at its barrier (which also frees the stage it reuses).
+    // Before issuing k-tile q into stage q % STAGES: once DEP - 1 tiles are in
+    // flight, wait until k-tile q - DEP + 1 has landed, then meet the consumers
+    // at its barrier.  Past it they have read k-tile q - STAGES, whose stage
+    // this is: DEP = STAGES hands it back at the barrier right after its reads (which
+    // therefore have to have returned), LATE one barrier later.
     auto gate = [&] {
       if (q >= DEP - 1) {
         wait_vmcnt<(DEP - 2) * NQ>();
@@ -878,7 +880,7 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
         qs = qs + 1 == STAGES ? 0 : qs + 1;
       }
     }
-    // Drain: the last min(nk, STAGES - 1) barriers; k-tile b has nk - 1 - b
+    // Drain: the last min(nk, DEP - 1) barriers; k-tile b has nk - 1 - b
     // younger tiles in flight.
     for (int b = max(0, nk - DEP + 1); b < nk; ++b) {
       const int younger = nk - 1 - b;
@@ -965,43 +967,43 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
         compute(B1{}, kt + 1);
       }
     } else {
-    bf16x8_t af[2][TM], bfr[2][TN];
-    auto read_frags = [&](const uint16_t *S, int ks, int buf, int kt) {
-      const int ch = ((2 * ks + lh) ^ sw) * 8;
+      bf16x8_t af[2][TM], bfr[2][TN];
+      auto read_frags = [&](const uint16_t *S, int ks, int buf, int kt) {
+        const int ch = ((2 * ks + lh) ^ sw) * 8;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[buf][i] = *reinterpret_cast<const bf16x8_t *>(S + aoff[i] + ch);
+        for (int i = 0; i < TM; ++i) af[buf][i] = *reinterpret_cast<const bf16x8_t *>(S + aoff[i] + ch);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) bfr[buf][j] = *reinterpret_cast<const bf16x8_t *>(S + boff[j] + ch);
-      if constexpr (PRE) {
-        const float *ps = pre_s + kt * BK + (2 * ks + lh) * 8;
-        const float4 s0 = *reinterpret_cast<const float4 *>(ps), s1 = *reinterpret_cast<const float4 *>(ps + 4);
-        const float4 h0 = *reinterpret_cast<const float4 *>(ps + kPreMax);
-        const float4 h1 = *reinterpret_cast<const float4 *>(ps + kPreMax + 4);
+        for (int j = 0; j < TN; ++j) bfr[buf][j] = *reinterpret_cast<const bf16x8_t *>(S + boff[j] + ch);
+        if constexpr (PRE) {
+          const float *ps = pre_s + kt * BK + (2 * ks + lh) * 8;
+          const float4 s0 = *reinterpret_cast<const float4 *>(ps), s1 = *reinterpret_cast<const float4 *>(ps + 4);
+          const float4 h0 = *reinterpret_cast<const float4 *>(ps + kPreMax);
+          const float4 h1 = *reinterpret_cast<const float4 *>(ps + kPreMax + 4);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) af[buf][i] = preact8(af[buf][i], s0, s1, h0, h1);
-      }
-    };
-    int cs = 0;  // stage of k-tile kt
-    for (int kt = 0; kt < nk; ++kt) {
-      __builtin_amdgcn_s_barrier();
-      const uint16_t *S = smem + cs * SM::kStage;
-      cs = cs + 1 == STAGES ? 0 : cs + 1;
-      read_frags(S, 0, 0, kt);
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<KS>([&](auto ksc) {
-        constexpr int ks = decltype(ksc)::value;
-        constexpr int cur = ks & 1;
-        if constexpr (ks + 1 < KS) read_frags(S, ks + 1, cur ^ 1, kt);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = EPI ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cur][j], af[cur][i], acc[i][j], 0, 0, 0)
-                            : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
-        sched_step<0, TM * TN, (ks + 1 < KS) ? TM + TN : 0, 0>();
+          for (int i = 0; i < TM; ++i) af[buf][i] = preact8(af[buf][i], s0, s1, h0, h1);
+        }
+      };
+      int cs = 0;  // stage of k-tile kt
+      for (int kt = 0; kt < nk; ++kt) {
+        __builtin_amdgcn_s_barrier();
+        const uint16_t *S = smem + cs * SM::kStage;
+        cs = cs + 1 == STAGES ? 0 : cs + 1;
+        read_frags(S, 0, 0, kt);
         __builtin_amdgcn_sched_barrier(0);
-      });
-    }
+        static_for<KS>([&](auto ksc) {
+          constexpr int ks = decltype(ksc)::value;
+          constexpr int cur = ks & 1;
+          if constexpr (ks + 1 < KS) read_frags(S, ks + 1, cur ^ 1, kt);
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              acc[i][j] = EPI ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cur][j], af[cur][i], acc[i][j], 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
+          sched_step<0, TM * TN, (ks + 1 < KS) ? TM + TN : 0, 0>();
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      }
     }
   }
 
@@ -1807,8 +1809,8 @@ hipError_t launch_ws_ld(const ConvArgs &a, hipStream_t s) {
 // Tile shape per layer.  Every shape uses the same k-tile and MFMA, so the
 // choice never changes a result bit.
 // A split output stored as NCHW from the epilogue: the warp-specialised
-// kernel with the LDS-staged epilogue, in the tile shape the layer would get
-// (tile shapes never change results).
+// kernel with the LDS-staged epilogue, on few tile shapes of its own (one launch
+// a pass; tile shapes never change results).
 template <int LD>
 hipError_t launch_nchw_out(const ConvArgs &a, hipStream_t s) {
   if (!ws_eligible(a, (Loader)LD) || LD == LD_S2D || a.N % 8) return hipErrorNotSupported;
@@ -1853,8 +1855,13 @@ inline bool pp_pays(const ConvArgs &a, Loader ld) {
   if (a.lanes > 1 && r > 2) return true;
   if (a.res && a.N >= 1024) return 8 * t > (a.K < 512 && r > 1 && a.lanes <= 1 ? 7 : 6) * cus * r;
   const bool wide = ld == LD_GEMM && a.N >= 2048 && a.K <= 1024;
-  const int f = ld != LD_CAT && a.kh == 1 && a.K < 512 ? 57 : 60;
-  const int g = a.res ? 16 : wide || ld == LD_CAT ? 9 : a.N < 512 ? 16 : a.K >= 2048 ? 10 : a.kh == 1 && a.K >= 512 ? 8 : 16;
+  const int f = ld != LD_CAT && a.kh == 1 && a.K < 512 ? 57 : 60;  // hundredths
+  const int g = a.res                          ? 16
+                : wide || ld == LD_CAT         ? 9
+                : a.N < 512                    ? 16
+                : a.K >= 2048                  ? 10
+                : a.kh == 1 && a.K >= 512      ? 8
+                                               : 16;  // sixteenths
   return 100 * r < f * ro || 16 * t > g * cus * r;
 }
 

@@ -43,13 +43,11 @@ __device__ __forceinline__ float4 load_a_chunk_f32(const ConvArgs &a, const RowS
   return v;
 }
 
-template <int BM, int BN, int LD>
+// Register-staged tiles of 64 x 64, double-buffered, for what the DMA kernel
+// below cannot address (f32_dma_fits).
+template <int LD>
 __global__ __launch_bounds__(kThreads) void conv_f32_kernel(ConvArgs a) {
-  constexpr int WN = 2;
-  constexpr int TM = BM / 64, TN = BN / 64;
-  constexpr int A_PER = BM * (BKF / 4) / kThreads;  // float4 chunks per thread
-  constexpr int B_PER = BN * (BKF / 4) / kThreads;
-  static_assert(TM >= 1 && TN >= 1 && A_PER >= 1 && B_PER >= 1, "tile");
+  constexpr int BM = 64, BN = 64;  // four waves of 32 x 32, one float4 chunk of A and B per thread
 
   __shared__ __attribute__((aligned(16))) float smem[2 * (BM + BN) * LDSF];
 
@@ -59,14 +57,12 @@ __global__ __launch_bounds__(kThreads) void conv_f32_kernel(ConvArgs a) {
 
   const int t = threadIdx.x;
   const int kc = t & 3;   // float4 chunk of the 16-wide k-tile
-  const int r0 = t >> 2;  // first row; then every 64th
+  const int r0 = t >> 2;  // row
 
-  RowState rs[A_PER];
-#pragma unroll
-  for (int i = 0; i < A_PER; ++i) rs[i] = make_row<LD>(a, m0 + r0 + 64 * i);
+  const RowState rs = make_row<LD>(a, m0 + r0);
 
   const float *wp = static_cast<const float *>(a.w);
-  float4 ra[A_PER], rb[B_PER];
+  float4 ra, rb;
   auto load_tile = [&](int kt) {
     const int kbase = kt * BKF;
     int kh_ = 0, kw_ = 0, c0 = 0;
@@ -76,35 +72,24 @@ __global__ __launch_bounds__(kThreads) void conv_f32_kernel(ConvArgs a) {
       kh_ = tap / a.kw;
       kw_ = tap - kh_ * a.kw;
     }
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i) ra[i] = load_a_chunk_f32<LD>(a, rs[i], kbase + kc * 4, kh_, kw_, c0);
-#pragma unroll
-    for (int j = 0; j < B_PER; ++j) {
-      const int n = n0 + r0 + 64 * j;
-      rb[j] = (n < a.N) ? *reinterpret_cast<const float4 *>(wp + (size_t)n * a.Kp + kbase + kc * 4)
-                        : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    ra = load_a_chunk_f32<LD>(a, rs, kbase + kc * 4, kh_, kw_, c0);
+    const int n = n0 + r0;
+    rb = (n < a.N) ? *reinterpret_cast<const float4 *>(wp + (size_t)n * a.Kp + kbase + kc * 4)
+                   : make_float4(0.f, 0.f, 0.f, 0.f);
   };
   auto store_tile = [&](int buf) {
-    float *As = smem + buf * (BM + BN) * LDSF;
-    float *Bs = As + BM * LDSF;
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i) *reinterpret_cast<float4 *>(As + (r0 + 64 * i) * LDSF + kc * 4) = ra[i];
-#pragma unroll
-    for (int j = 0; j < B_PER; ++j) *reinterpret_cast<float4 *>(Bs + (r0 + 64 * j) * LDSF + kc * 4) = rb[j];
+    float *As = smem + buf * (BM + BN) * LDSF + r0 * LDSF + kc * 4;
+    *reinterpret_cast<float4 *>(As) = ra;
+    *reinterpret_cast<float4 *>(As + BM * LDSF) = rb;
   };
 
   const int lane = t & 63, wave = t >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave >> 1, wn = wave & 1;
   const int lrow = lane & 31, lk = (lane >> 5) * 8;
 
-  f32x16_t acc[TM][TN];
+  f32x16_t acc;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 
   // k-tiles [kt0, kt1): slice blockIdx.y of a split reduction, or all of them.
   const int nk_all = a.Kp / BKF;
@@ -116,76 +101,44 @@ __global__ __launch_bounds__(kThreads) void conv_f32_kernel(ConvArgs a) {
   for (int kt = kt0; kt < kt1; ++kt) {
     const int cur = (kt - kt0) & 1;
     if (kt + 1 < kt1) load_tile(kt + 1);
-    const float *As = smem + cur * (BM + BN) * LDSF + (wm * TM * 32 + lrow) * LDSF + lk;
-    const float *Bs = smem + cur * (BM + BN) * LDSF + BM * LDSF + (wn * TN * 32 + lrow) * LDSF + lk;
+    const float *As = smem + cur * (BM + BN) * LDSF + (wm * 32 + lrow) * LDSF + lk;
+    const float *Bs = smem + cur * (BM + BN) * LDSF + BM * LDSF + (wn * 32 + lrow) * LDSF + lk;
     // Lane half h feeds k = 8h + s at step s to both operands, so the 8 steps
     // cover the 16 k of the tile exactly once.
-    float av[TM][8], bv[TN][8];
+    const float4 pa = *reinterpret_cast<const float4 *>(As), qa = *reinterpret_cast<const float4 *>(As + 4);
+    const float4 pb = *reinterpret_cast<const float4 *>(Bs), qb = *reinterpret_cast<const float4 *>(Bs + 4);
+    const float av[8] = {pa.x, pa.y, pa.z, pa.w, qa.x, qa.y, qa.z, qa.w};
+    const float bv[8] = {pb.x, pb.y, pb.z, pb.w, qb.x, qb.y, qb.z, qb.w};
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const float4 p = *reinterpret_cast<const float4 *>(As + i * 32 * LDSF);
-      const float4 q = *reinterpret_cast<const float4 *>(As + i * 32 * LDSF + 4);
-      av[i][0] = p.x; av[i][1] = p.y; av[i][2] = p.z; av[i][3] = p.w;
-      av[i][4] = q.x; av[i][5] = q.y; av[i][6] = q.z; av[i][7] = q.w;
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const float4 p = *reinterpret_cast<const float4 *>(Bs + j * 32 * LDSF);
-      const float4 q = *reinterpret_cast<const float4 *>(Bs + j * 32 * LDSF + 4);
-      bv[j][0] = p.x; bv[j][1] = p.y; bv[j][2] = p.z; bv[j][3] = p.w;
-      bv[j][4] = q.x; bv[j][5] = q.y; bv[j][6] = q.z; bv[j][7] = q.w;
-    }
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i][s], bv[j][s], acc[i][j], 0, 0, 0);
+    for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], bv[s], acc, 0, 0, 0);
     if (kt + 1 < kt1) store_tile(cur ^ 1);
     __syncthreads();
   }
 
+  const int n = n0 + wn * 32 + lrow;
+  if (n >= a.N) return;
+  const int mb = m0 + wm * 32 + 4 * (lane >> 5);
   if (S > 1) {  // partial sums of this slice; bias and activation come after the sum
     float *part = a.part + (int64_t)blockIdx.y * a.M * a.N;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int n = n0 + wn * TN * 32 + j * 32 + lrow;
-      if (n >= a.N) continue;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = m0 + wm * TM * 32 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (m < a.M) part[(int64_t)m * a.N + n] = acc[i][j][r];
-        }
+    for (int r = 0; r < 16; ++r) {
+      const int m = mb + 8 * (r >> 2) + (r & 3);
+      if (m < a.M) part[(int64_t)m * a.N + n] = acc[r];
     }
     return;
   }
   float *y = static_cast<float *>(a.y);
   const float *res = static_cast<const float *>(a.res);
+  const float bias = a.bias ? a.bias[n] : 0.0f;
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = n0 + wn * TN * 32 + j * 32 + lrow;
-    if (n >= a.N) continue;
-    const float bvv = a.bias ? a.bias[n] : 0.0f;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * TM * 32 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (m >= a.M) continue;
-        float v = acc[i][j][r] + bvv;
-        if (res) v += res[(int64_t)m * a.ldr + n];
-        y[(int64_t)m * a.ldc + n] = epilogue_act(v, a.relu, a.gelu);
-      }
-    }
+  for (int r = 0; r < 16; ++r) {
+    const int m = mb + 8 * (r >> 2) + (r & 3);
+    if (m >= a.M) continue;
+    float v = acc[r] + bias;
+    if (res) v += res[(int64_t)m * a.ldr + n];
+    y[(int64_t)m * a.ldc + n] = epilogue_act(v, a.relu, a.gelu);
   }
 }
-
-
-// The register-staged kernel above takes what the DMA kernel's 31-bit byte
-// offsets and tap table cannot address (f32_dma_fits).
 
 // ------------------------------------------------------- LDS-DMA pipeline
 
@@ -455,12 +408,12 @@ __global__ void f32_split_reduce_kernel(ConvArgs a) {
   for (int e = 0; e < 4; ++e) y[m * a.ldc + n + e] = o[e];
 }
 
-template <int BM, int BN, int LD>
-hipError_t launch_f32_cfg(const ConvArgs &a, hipStream_t s) {
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+template <int LD>
+hipError_t launch_f32_staged(const ConvArgs &a, hipStream_t s) {
+  const int tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
   const int S = a.splits > 1 ? a.splits : 1;
   if (S > 1 && (!a.part || a.N % 4 != 0 || a.Kp / BKF < S)) return hipErrorInvalidValue;
-  hapi_launch((conv_f32_kernel<BM, BN, LD>), dim3(tiles, S), dim3(kThreads), 0, s, a);
+  hapi_launch(conv_f32_kernel<LD>, dim3(tiles, S), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -500,10 +453,10 @@ hipError_t launch_conv_f32(const ConvArgs &a, Loader ld, hipStream_t s) {
     case LD_NHWC:
     case LD_GEMM:
       if (dma) return launch_f32_ld<LD_NHWC>(a, s);
-      return ld == LD_NHWC ? launch_f32_cfg<64, 64, LD_NHWC>(a, s) : launch_f32_cfg<64, 64, LD_GEMM>(a, s);
+      return ld == LD_NHWC ? launch_f32_staged<LD_NHWC>(a, s) : launch_f32_staged<LD_GEMM>(a, s);
     case LD_NCHW:
       if (dma) return launch_f32_ld<LD_NCHW>(a, s);
-      return launch_f32_cfg<64, 64, LD_NCHW>(a, s);
+      return launch_f32_staged<LD_NCHW>(a, s);
     default: break;
   }
   return hipErrorInvalidValue;

@@ -373,7 +373,10 @@ hipError_t launch_ek(const PPArgs &pa, hipStream_t s) {
     if constexpr (LD == LD_GEMM) return launch<LD, KW, 1>(pa, s);
     return hipErrorNotSupported;
   }
-  if (pa.a.res) return launch<LD, KW, 3>(pa, s);
+  if (pa.a.res) {
+    if constexpr (LD == LD_GEMM || (LD == LD_NHWC && KW == 3)) return launch<LD, KW, 3>(pa, s);
+    return hipErrorNotSupported;
+  }
   return launch<LD, KW, 0>(pa, s);
 }
 
@@ -388,6 +391,7 @@ bool conv_pp_supported(const ConvArgs &a, Loader ld) {
   if (ld == LD_GEMM) return !a.pool && (int64_t)a.M * (a.lda ? a.lda : a.K) * 2 < lim;
   if (ld != LD_NHWC && ld != LD_CAT) return false;
   if (a.gelu || a.C % BK || a.kh != a.kw || (a.kh != 1 && a.kh != 3)) return false;
+  if (a.res && (ld == LD_CAT || a.kh == 1)) return false;  // residuals of 3 x 3 and plain 1 x 1 layers only
   if ((int64_t)a.n_img * a.H * a.W * a.C * 2 >= lim) return false;
   return ld == LD_NHWC ? !a.pool || a.kh == 3 : a.C2 % BK == 0 && (int64_t)a.n_img * a.H2 * a.W2 * a.C2 * 2 < lim;
 }

@@ -117,9 +117,10 @@ struct ConvArgs {
   // loader, ReLU, even Ho and Wo, N % 16 == 0, no residual; launch_conv_bf16
   // returns hipErrorNotSupported, having launched nothing, otherwise.
   int pool;
-  // fp32 only: the k-tiles split into `splits` consecutive slices computed by
-  // separate workgroups into part [splits][M][N] (float32), then summed in
-  // slice order (fixed, so results do not depend on M); splits <= 1: none.
+  // fp32 only: the k-tiles split into `splits` consecutive slices, summed in
+  // slice order (fixed, so results do not depend on M): by one workgroup per tile
+  // (f32_seq), or by separate workgroups into part [splits][M][N] (float32) and
+  // launch_f32_split_reduce.  splits <= 1: one slice.
   float *part;
   int splits;
 };
