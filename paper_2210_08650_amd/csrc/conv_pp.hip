@@ -1,5 +1,5 @@
 // Implicit-GEMM convolution / linear kernel on 256 x 256 output tiles (bf16,
-// gfx950), for layers with enough tiles to fill the chip.
+// gfx950), for layers whose rounds of such tiles fill the chip.
 //
 // Eight waves, two per SIMD, all load and compute: wave (g, c) owns rows
 // 64 g .. + 63 of both 128-row halves of A and columns 32 c .. + 31 of both
@@ -16,15 +16,17 @@
 // of a stage is loaded again as soon as both groups have read it, so a DMA has
 // about a k-tile's time to land and the wait never drains the queue.
 //
-// What bounds it: without its DMAs it runs an 8192 x 4096 x 8192 product at
-// 1.64 PF/s on random data (the clock the chip holds under full MFMA load; 2.09
-// on zeros), with them at 1.46-1.52 PF/s (the 128 x 256 tiles: 1.09-1.29;
-// the vendor library 1.37-1.46 on 8192^3).  On a model's layers the rounds
-// of tiles over 256 CUs, the stores of a round of tiles at once (they share the
-// loads' counter) and GELU cost more: ViT-B/16 qkv at 64 images (450 tiles of
-// 12 k-tiles) 57 -> 48 us, fc2 78 -> 61 us, ResNet-50 stage-3 shortcut GEMM
-// 53 -> 46 us, VGG-16 conv4_2 at 64 images 222 -> 198 us.  Measured and slower:
-// four slots of 8 MFMAs per k-tile (qkv 53 us), reading each fragment into the
+// What bounds it: an 8192 x 4096 x 8192 product on random data, back to back, runs
+// at 1.36 PF/s (256 x 128 tiles of the persistent kernel 1.12-1.20, the vendor
+// library 1.29-1.57 from run to run).  On a model's layers the rounds of tiles over
+// 256 CUs, the stores of a round of tiles at once (they share the loads' counter),
+// the residual's loads and GELU cost more: the matrix pipes are busy on 44-48% of
+// the cycles in VGG-16's layers at 128 images and 27-32% in ViT-B/16's, with waves
+// waiting 27-33% of theirs and no bank conflicts.  Against the kernels those layers
+// ran on: ViT-B/16 qkv at 64 images (450 tiles of 12 k-tiles) 62 -> 51 us, fc2
+// 81 -> 67 us, ResNet-50's stage-3 shortcut GEMM at 128 images 58 -> 51 us, VGG-16
+// conv4_2 at 64 images 262 -> 216 us.  Measured and slower (qkv at 48 us then):
+// four slots of 8 MFMAs per k-tile (53 us), reading each fragment into the
 // register its predecessor leaves, without groups (52 us), raised wave
 // priority around the MFMAs (1-3%), one workgroup per tile instead of the
 // persistent loop (50 us).
