@@ -254,14 +254,19 @@ bool stem_pool_supported(int C, int H, int W, int cout, int Ho, int Wo, int Hp, 
 
 hipError_t launch_stem_pool_bf16(const void *x, const void *w, int ldw, const float *bias, void *y, int n, int C,
                                  int H, int W, int Ho, int Wo, int Hp, int Wp, int cus, hipStream_t s) {
-  // Two bands per image, or enough for one workgroup per CU, with at least
-  // two pooled rows per band (each band recomputes one conv row of halo:
-  // ResNet-50 b8, 224 workgroups of two rows instead of 112 of four, 419 -> 413 us,
-  // ResNet-18 b8 121 -> 116 us).
+  // Two bands per image, or enough for one workgroup per CU, with at least four
+  // pooled rows per band (each band recomputes one conv row of halo).  Bands of
+  // two or three rows as long as they all run at once (ResNet-50 b8, 224
+  // workgroups of two rows instead of 112 of four, 419 -> 413 us, ResNet-18 b8
+  // 121 -> 116 us); a workgroup more than CUs is a second round (21 images of
+  // 192 x 192: 273 of them 30.0 us, 252 with four rows 23.7 us).
   int bands = n > 0 ? (cus + n - 1) / n : 2;
   bands = bands < 2 ? 2 : bands;
-  const int max_bands = Hp / 2 < 2 ? 2 : Hp / 2;
-  bands = bands > max_bands ? max_bands : bands;
+  const int four = Hp / 4 < 2 ? 2 : Hp / 4, two = Hp / 2 < 2 ? 2 : Hp / 2;
+  if (bands > four) {
+    const int fit = cus / n < two ? cus / n : two;
+    bands = fit > four ? fit : four;
+  }
   bands = bands > Hp ? Hp : bands;
   StemArgs a{static_cast<const uint16_t *>(x), static_cast<const uint16_t *>(w), bias, static_cast<uint16_t *>(y),
              n, C, H, W, ldw, Ho, Wo, Hp, Wp, bands};

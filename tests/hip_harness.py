@@ -6,6 +6,10 @@ come from the oracle, computed on the CPU from the same synthetic arrays.
 """
 from __future__ import annotations
 
+import json
+import os
+import tempfile
+
 import numpy as np
 import torch
 
@@ -77,6 +81,22 @@ def kernel_names(call):
             n = e.name.removeprefix("void ").replace("hapi::", "").replace("(anonymous namespace)::", "")
             names.append(n.replace("(Loader)", "").split("(")[0])
     return names
+
+
+def kernel_grids(call):
+    """(name up to its template arguments, workgroups) of the library's kernels that ``call`` launches."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+        call()
+        torch.cuda.synchronize()
+    with tempfile.TemporaryDirectory() as d:
+        p.export_chrome_trace(os.path.join(d, "trace.json"))
+        with open(os.path.join(d, "trace.json")) as f:
+            events = json.load(f)["traceEvents"]
+    return [(e["name"].removeprefix("void ").replace("hapi::", "").replace("(anonymous namespace)::", "")
+             .split("<")[0].split("(")[0], int(np.prod(e["args"]["grid"])))
+            for e in events if e.get("cat") == "kernel" and "hapi::" in e["name"]]
 
 
 def assert_routes(call, wanted=(), unwanted=()):

@@ -5,11 +5,12 @@ compare them bit for bit); times do: a route taken at a size where another kerne
 faster is the fault these cases pin.  Sizes lie on both sides of each rule.
 """
 import pytest
+import torch
 
 import paper_2210_08650_amd as H
 from paper_2210_08650_amd import models as PM
 import synth
-from tests.hip_harness import Runner, assert_routes, images_for
+from tests.hip_harness import Runner, assert_routes, images_for, kernel_grids
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +66,26 @@ def test_route(name):
     xd, _ = images_for(H.HAPI_BF16, synth.images(15, 1, *in_shape))
     xd = xd.expand(batch, *in_shape).contiguous()
     assert_routes(lambda: r.extract(xd, split, inflight=inflight, chunk=-(-batch // inflight)), wanted, unwanted)
+
+
+@pytest.mark.parametrize("side,batch,workgroups", [
+    (224, 8, 224),     # bands of two pooled rows: 28 an image
+    (224, 16, 256),    # one for every CU
+    (192, 21, 252),    # 13 bands an image would be 273 workgroups: 12, of four rows
+    (256, 13, 247),    # 20 would be 260: 19
+    (224, 40, 280),    # from about 19 images on, bands of four rows and more, a workgroup per CU
+    (224, 130, 260),   # two bands an image
+])
+def test_stem_bands(side, batch, workgroups):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("counted for 256 CUs")
+    layers = PM.resnet18()[:3]
+    raw = synth.params(16, PM.raw_manifest(layers, (3, side, side)))
+    print(f"case {batch} images of {side}", flush=True)
+    r = Runner(layers, H.HAPI_BF16, raw, (3, side, side))
+    xd = torch.zeros((batch, 3, side, side), dtype=torch.bfloat16, device="cuda")
+    for _ in range(3):  # the tracer can drop records
+        got = [n for k, n in kernel_grids(lambda: r.extract(xd, 3, inflight=1, chunk=batch)) if k == "stem_pool_kernel"]
+        if got:
+            break
+    assert got == [workgroups]
