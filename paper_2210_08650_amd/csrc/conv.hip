@@ -1949,12 +1949,17 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
       return launch_pws_ld<128, 256, 2, 4, 4, 3, LD, 2>(a, s);
     } else if (a.N <= 128) {
       if (a.kh == 1 && a.K <= 256 && a.K >= 2 * BK) return launch_pws_ld<256, 128, 4, 2, 4, 3, LD, 2>(a, s);
-      // 3 x 3 over 64 channels to 128 (VGG conv2_1), or any with a round and a half
-      // of 256 x 128 tiles: those on the persistent kernel (VGG-16 b128
-      // +1.6%; 128 -> 128 channels: 196 tiles 26.1 against 25.1 us, 294 tiles 40.2
-      // against 38.7 us, 392 tiles 40.2 against 41.7 us, 1,764 tiles 144 against
-      // 154 us; two partitions of 319 tiles, ResNet-18 b208: 819 us in all against 764)
-      if (a.kh == 3 && a.K >= 2 * BK && (a.K <= 9 * 64 || 2 * ((a.M + 255) / 256) >= 3 * a.cus))
+      // 3 x 3 over 64 channels to 128 (VGG conv2_1), or any with two rounds of 256 x 128
+      // tiles filled to 3/4, or more to 7/8: those on the persistent kernel (VGG-16
+      // b128 +1.6%; 128 -> 128 channels: 196 tiles 26.1 against 25.1 us, 294 tiles 40.2
+      // against 38.7 us, 392 tiles 40.2 against 41.7 us, 552 tiles, 0.72 of three
+      // rounds, 60.2 against 59.8, 1,176 tiles, 0.92 of five, 101 against 106, 1,764
+      // tiles 144 against 154; in whole passes two partitions of 319 tiles,
+      // ResNet-18 b208, 819 us against 764, and VGG-16's block 2 at 21 images, 1,029
+      // tiles, 215 against 211, at 13 images, 637 tiles, 137 against 136)
+      const int cus = a.cus > 0 ? a.cus : cu_count(), t256 = (a.M + 255) / 256, rounds = (t256 + cus - 1) / cus;
+      if (a.kh == 3 && a.K >= 2 * BK &&
+          (a.K <= 9 * 64 || (rounds > 1 && 16 * (int64_t)t256 >= (rounds > 2 ? 14 : 12) * (int64_t)rounds * cus)))
         return launch_pws_ld<256, 128, 4, 2, 4, 3, LD, 2>(a, s);
       // 1 x 1 with K >= 512 (ResNet-50 stage-2 reductions): with partitions
       // in flight persistent 256 x 128 tiles (b256 +1.0%, b512 +0.8%), alone

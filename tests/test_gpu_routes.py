@@ -50,9 +50,12 @@ CASES = {
     "3x3 of 36 k-tiles": (_conv(256, 256, 3, 14, 48), ["conv_bf16_pws_kernel<128, 128"], [W64]),
     "1x1 of 12 k-tiles": (_conv(768, 768, 1, 14, 16), [W64L], []),
     "1x1 of 48 k-tiles": (_conv(3072, 768, 1, 14, 16), ["conv_bf16_pws_kernel<128, 128"], [W64L]),
-    # 128-channel 3 x 3s: the persistent kernel from a round and a half of 256-row tiles on
+    # 128-channel 3 x 3s: the persistent kernel where two rounds of 256-row tiles are filled to 3/4,
+    # more rounds to 7/8
     "3x3 to 128, 294 tiles": (_conv(128, 128, 3, 56, 24), [], [TALL]),
     "3x3 to 128, 392 tiles": (_conv(128, 128, 3, 56, 32), [TALL], []),
+    "3x3 to 128, 698 tiles": (_conv(128, 128, 3, 56, 57), [TALL], []),
+    "3x3 to 128, 1029 tiles": (_conv(128, 128, 3, 56, 84), [], [TALL]),
     "3x3 to 128, two partitions of 319": (_conv(128, 128, 3, 28, 208, 2), [], [TALL]),
 }
 
