@@ -735,7 +735,9 @@ struct WsPlan {
   }
 };
 
-template <int BM, int BN, int WM, int WN, int STAGES, int LD, int KW, int EPI, bool PRE = false>
+// AHEAD: waves with one 32 x 32 block read a whole k-tile's fragments ahead of
+// its MFMAs; the others, and all without it, one k-step's.
+template <int BM, int BN, int WM, int WN, int STAGES, int LD, int KW, int EPI, bool PRE = false, bool AHEAD = true>
 __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
   constexpr int CW = WM * WN;                      // consumer waves (= producer waves)
   constexpr int NT = 2 * CW * 64;
@@ -746,7 +748,7 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
   // k-tiles in flight or being read: with 1 x 1 fragments per wave and a deep
   // ring, a stage is handed back one barrier later, so that no barrier waits
   // for fragment reads to return.
-  constexpr bool LATE = TM * TN == 1 && STAGES >= 5;
+  constexpr bool LATE = AHEAD && TM * TN == 1 && STAGES >= 5;
   constexpr int DEP = LATE ? STAGES - 1 : STAGES;
   using SM = PipeSmem<BM, BN, STAGES, EPI>;
   using Plan = WsPlan<NA, NB, LD, KW>;
@@ -905,7 +907,7 @@ __device__ __forceinline__ void conv_bf16_ws_body(const ConvArgs &a) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) boff[j] = BM * BK + (wn * TN * 32 + j * 32 + lrow) * BK;
     const int sw = (lrow >> 1) & 7;
-    if constexpr (TM * TN == 1) {
+    if constexpr (AHEAD && TM * TN == 1) {
       // One MFMA per k-step cannot hide the latency of the next step's reads:
       // the whole next k-tile's fragments are read while this one's MFMAs run
       // (ResNet-50 b8 450 -> 428 us, b16 521 -> 481 us; with the later hand-back
@@ -1187,6 +1189,12 @@ __global__ __launch_bounds__(2 * WM * WN * 64) void conv_bf16_ws_kernel(ConvArgs
 template <int BM, int BN, int WM, int WN, int STAGES, int LD, int KW, int EPI, bool PRE = false>
 __global__ __launch_bounds__(2 * WM * WN * 64, 2) void conv_bf16_ws2_kernel(ConvArgs a) {
   conv_bf16_ws_body<BM, BN, WM, WN, STAGES, LD, KW, EPI, PRE>(a);
+}
+
+// Two workgroups per CU, fragments of one k-step ahead (launch_ws_64).
+template <int BM, int BN, int WM, int WN, int STAGES, int LD, int KW, int EPI>
+__global__ __launch_bounds__(2 * WM * WN * 64, 2) void conv_bf16_ws2_step_kernel(ConvArgs a) {
+  conv_bf16_ws_body<BM, BN, WM, WN, STAGES, LD, KW, EPI, false, false>(a);
 }
 
 template <int BM, int BN, int WM, int WN, int STAGES, int LD, int KW, int EPI>
@@ -1806,6 +1814,27 @@ hipError_t launch_ws_ld(const ConvArgs &a, hipStream_t s) {
   return launch_ws_cfg<BM, BN, WM, WN, STAGES, LD, 1, EPI, MINB>(a, s);
 }
 
+// 64 x 64 tiles, four stages.  Where up to a third of the CUs get a second
+// workgroup of a long reduction, one k-step's fragments ahead are faster than the
+// whole k-tile's, by how much depends on the box (VGG-16 from pool3 at 12 images,
+// 296 tiles in its last layers, 229 against 239 us on one, 225.6 against 224.1 on
+// another; ViT-B/16 at 7 images, 264 tiles of fc2, 590 against 609 us; 228 tiles of
+// it 13.2 against 12.3 us, 372 tiles 21.2 against 20.8).
+template <int LD, int EPI>
+hipError_t launch_ws_64(const ConvArgs &a, hipStream_t s) {
+  if constexpr (LD == LD_GEMM || LD == LD_NHWC || LD == LD_CAT) {
+    const int64_t t64 = (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64);
+    if (t64 > a.cus && 3 * t64 <= 4 * (int64_t)a.cus && a.K >= 32 * BK && (!a.pool || (EPI == 2 && LD == LD_NHWC))) {
+      if (a.kh == 3)
+        hapi_launch((conv_bf16_ws2_step_kernel<64, 64, 2, 2, 4, LD, 3, EPI>), dim3((int)t64), dim3(512), 0, s, a);
+      else
+        hapi_launch((conv_bf16_ws2_step_kernel<64, 64, 2, 2, 4, LD, 1, EPI>), dim3((int)t64), dim3(512), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  return launch_ws_ld<64, 64, 2, 2, 4, LD, EPI, 2>(a, s);
+}
+
 // Tile shape per layer.  Every shape uses the same k-tile and MFMA, so the
 // choice never changes a result bit.
 // A split output stored as NCHW from the epilogue: the warp-specialised
@@ -1815,7 +1844,7 @@ template <int LD>
 hipError_t launch_nchw_out(const ConvArgs &a, hipStream_t s) {
   if (!ws_eligible(a, (Loader)LD) || LD == LD_S2D || a.N % 8) return hipErrorNotSupported;
   if (a.lanes <= 1 && a.N >= 64 && 2 * (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) < a.cus)
-    return launch_ws_ld<64, 64, 2, 2, 4, LD, 0, 2>(a, s);
+    return launch_ws_64<LD, 0>(a, s);
   if (a.N <= 64) return launch_ws_ld<128, 64, 2, 2, 3, LD, 0, 2>(a, s);
   if (a.res && a.N >= 1024) return launch_ws_ld<128, 64, 2, 2, 2, LD, 0, 3>(a, s);
   return launch_ws_ld<128, 128, 2, 2, 2, LD, 0, 2>(a, s);
@@ -1921,7 +1950,7 @@ hipError_t launch_pipe_ld(const ConvArgs &a, hipStream_t s) {
     const bool short_k = a.K < 20 * BK && !(a.kh == 1 && a.N <= 128 && a.K >= 512);
     if (a.lanes <= 1 && a.N >= 64 &&
         8 * (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) < (short_k ? 5 : 4) * (int64_t)a.cus)
-      return launch_ws_ld<64, 64, 2, 2, 4, LD, 2, 2>(a, s);
+      return launch_ws_64<LD, 2>(a, s);
     if (a.lanes <= 1 && a.N >= 128 && a.K >= 1024 &&
         2 * (int64_t)((a.M + 255) / 256) * ((a.N + 127) / 128) < a.cus)
       return launch_pws_ld<128, 128, 2, 2, 4, 4, LD, 2>(a, s);

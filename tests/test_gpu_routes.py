@@ -50,6 +50,10 @@ CASES = {
     "3x3 of 36 k-tiles": (_conv(256, 256, 3, 14, 48), ["conv_bf16_pws_kernel<128, 128"], [W64]),
     "1x1 of 12 k-tiles": (_conv(768, 768, 1, 14, 16), [W64L], []),
     "1x1 of 48 k-tiles": (_conv(3072, 768, 1, 14, 16), ["conv_bf16_pws_kernel<128, 128"], [W64L]),
+    # 64 x 64 tiles of long reductions, one for each of the 256 CUs and up to a third of them more
+    "1x1 of 48 k-tiles, 264 tiles": (_conv(3072, 768, 1, 13, 8), ["conv_bf16_ws2_step_kernel"], [W64L]),
+    "1x1 of 48 k-tiles, 360 tiles": (_conv(3072, 768, 1, 13, 11), [W64L], ["conv_bf16_ws2_step_kernel"]),
+    "3x3 of 72 k-tiles, 264 tiles": (_conv(512, 512, 3, 11, 17), ["conv_bf16_ws2_step_kernel"], [W64]),
     # 128-channel 3 x 3s: the persistent kernel where two rounds of 256-row tiles are filled to 3/4,
     # more rounds to 7/8
     "3x3 to 128, 294 tiles": (_conv(128, 128, 3, 56, 24), [], [TALL]),

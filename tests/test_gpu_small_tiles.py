@@ -26,6 +26,9 @@ CASES = {
     "1x1, five k-tiles": ([POOL1, PM.conv(320, 128, 1), PM.conv(128, 64, 1)], (320, 13, 13), (1, 3, 40, 130), [RING32]),
     "1x1, six k-tiles": ([POOL1, PM.conv(384, 128, 1), PM.conv(128, 64, 1)], (384, 13, 13), (1, 3, 40, 130), [RING32]),
     "3x3, nine k-tiles": ([POOL1, PM.conv(64, 136, 3, 1, 1), POOL1], (64, 13, 13), (1, 3, 60, 160), [RING32]),
+    # 264 tiles of 64 x 64 at the second batch: long reductions, fragments one k-step ahead
+    "1x1, 48 k-tiles": ([POOL1, PM.conv(3072, 768, 1), PM.conv(768, 64, 1)], (3072, 13, 13), (1, 8, 30, 60), [RING32]),
+    "3x3, 72 k-tiles": ([POOL1, PM.conv(512, 512, 3, 1, 1), PM.conv(512, 64, 1)], (512, 11, 11), (1, 17, 40, 140), [RING32]),
     # the split layer: NCHW from the epilogue, on 64 x 64 and 128 x 128 tiles
     "3x3 split": ([POOL1, PM.conv(64, 136, 3, 1, 1)], (64, 13, 13), (1, 3, 40, 160), ["conv_bf16_ws2_kernel<64, 64, 2, 2, 4"]),
     "residual block": ([POOL1, dict(kind=H.HAPI_BOTTLENECK, cin=256, width=64, cout=256, stride=2),
