@@ -1816,7 +1816,7 @@ hipError_t launch_ws_ld(const ConvArgs &a, hipStream_t s) {
 
 // 64 x 64 tiles, four stages.  Where up to a third of the CUs get a second
 // workgroup of a long reduction, one k-step's fragments ahead are faster than the
-// whole k-tile's, by how much depends on the box (VGG-16 from pool3 at 12 images,
+// whole k-tile's, on some machines only (VGG-16 from pool3 at 12 images,
 // 296 tiles in its last layers, 229 against 239 us on one, 225.6 against 224.1 on
 // another; ViT-B/16 at 7 images, 264 tiles of fc2, 590 against 609 us; 228 tiles of
 // it 13.2 against 12.3 us, 372 tiles 21.2 against 20.8).
